@@ -72,6 +72,8 @@ struct Block {
   std::vector<int> ditab;   //   and their pair and mode indices
   int dn1 = 0, dn12 = 0;
   size_t off_dtab = 0, off_ditab = 0;
+  std::vector<double> mf;   // table image of the matrix-core stages
+  size_t off_mf = 0;
   std::vector<double> wref; // iso-parametric blocks: reference weights [Q^3]
   size_t off_xco = 0, off_wref = 0;
   bool iso() const { return d.geom == SHP_ISOPARAM; }
@@ -176,10 +178,15 @@ constexpr int HI_NT[4][4] = {{256, 512, 512, 512}, {512, 512, 512, 512}, {512, 5
 constexpr int HI_MESH_E[4] = {2, 1, 1, 1};
 constexpr int HI_MESH_NT[4] = {512, 256, 512, 512};
 
+// the collocated Laplacian / Helmholtz actions: FP64 ones that the matrix-core
+// launch can take, and all of them
+bool mf_action(int opk) { return opk == OPK_HELM || opk == OPK_LAP || opk == OPK_ADR; }
+bool helm_action(int opk) { return mf_action(opk) || opk == OPK_HELM_F32 || opk == OPK_LAP_F32; }
+
 Tiling default_tiling(int sh, int P, int opk, size_t lds_budget = 40 * 1024) {
   Tiling t;
   t.NT = 256;
-  const bool helm = (opk == OPK_HELM || opk == OPK_LAP || opk == OPK_ADR);
+  const bool helm = helm_action(opk);
   const long long Q3 = (long long)(P + 2) * (P + 2) * (P + 2);
   if (is_2d(sh)) {
     const int Q = P + 2;
@@ -209,6 +216,7 @@ Tiling default_tiling(int sh, int P, int opk, size_t lds_budget = 40 * 1024) {
     t.persist = 0;
     return t;
   }
+  if (int E, NT; mf_action(opk) && mf_helm_shape(P, &E, &NT)) return Tiling{E, NT, 2};
   if (helm && P >= 7) {
     t.E = HI_E[sh][P - 7];
     t.NT = HI_NT[sh][P - 7];
@@ -216,7 +224,7 @@ Tiling default_tiling(int sh, int P, int opk, size_t lds_budget = 40 * 1024) {
     return t;
   }
   int E = 1;
-  while (E < 16 && op_lds_bytes(sh, P, opk, E + 1, 2) <= lds_budget && (!helm || (E + 1) * Q3 <= 4LL * t.NT)) ++E;
+  while (E < 16 && op_lds_bytes(sh, P, helm ? (int)OPK_HELM : opk, E + 1, 2) <= lds_budget && (!helm || (E + 1) * Q3 <= 4LL * t.NT)) ++E;
   t.E = E;
   t.persist = points_per_thread((long long)E * (P + 2) * (P + 2) * (P + 2), t.NT) > 0 ? 2 : 0;
   return t;
@@ -362,6 +370,7 @@ int shp_plan_create(shp_plan* out, const shp_block_desc* blk, int nblk) {
     B.NP = num_modes(B.d.shape, B.d.P);
     B.NQ = B.d.Q * B.d.Q * B.d.Q;
     build_tables(B.d.shape, B.d.P, B.d.pts, B.tab, B.itab);
+    build_mf_image(B.d.shape, B.d.P, B.tab, B.itab, B.mf);
     build_diag_tables(B.d.shape, B.d.P, B.d.pts, B.dtab, B.ditab, B.dn1, B.dn12);
     if (B.iso()) build_ref_weights(B.d.shape, B.d.P, B.d.pts, B.wref);
     if (B.d.P <= LOCALMAT_MAX_P && !B.iso()) {
@@ -422,6 +431,8 @@ int shp_plan_create(shp_plan* out, const shp_block_desc* blk, int nblk) {
     off = align_up(off + sizeof(uint16_t) * B.am16.size());
     B.off_am32 = off;
     off = align_up(off + sizeof(float) * B.am32.size());
+    B.off_mf = off;
+    off = align_up(off + sizeof(double) * B.mf.size());
     B.off_dtab = off;
     off = align_up(off + sizeof(double) * B.dtab.size());
     B.off_ditab = off;
@@ -530,6 +541,8 @@ int shp_plan_bind_workspace(shp_plan p, void* ws, size_t ws_bytes, void* stream)
                          s);
     if (e == hipSuccess && B.iso())
       e = hipMemcpyAsync(p->ws + B.off_wref, B.wref.data(), sizeof(double) * B.wref.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && !B.mf.empty())
+      e = hipMemcpyAsync(p->ws + B.off_mf, B.mf.data(), sizeof(double) * B.mf.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess && !B.dtab.empty())
       e = hipMemcpyAsync(p->ws + B.off_dtab, B.dtab.data(), sizeof(double) * B.dtab.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess && !B.ditab.empty())
@@ -684,6 +697,23 @@ int shp_block_offsets(shp_plan p, int blk, int64_t* coeff_off, int64_t* phys_off
   return SHP_OK;
 }
 
+// the tile lists of whole-mesh operator opk (and of the FP32 actions that
+// follow its launch shape) no longer hold
+static void drop_tiles(shp_plan p, int opk) {
+  p->mixed_dirty[opk] = true;
+  if (opk == OPK_HELM) p->mixed_dirty[OPK_HELM_F32] = true;
+  if (opk == OPK_LAP) p->mixed_dirty[OPK_LAP_F32] = true;
+}
+
+static void set_tiling_raw(shp_plan p, int blk, int opk, const Tiling& t) {
+  if (blk >= 0)
+    p->blocks[blk].tiling[opk] = t;
+  else {
+    p->mixed[opk] = t;
+    drop_tiles(p, opk);
+  }
+}
+
 int shp_set_tiling(shp_plan p, int blk, int op, int strategy, int E, int NT, int persistent) {
   if (int r = check_plan(p)) return r;
   const bool dim2 = is_2d(p->blocks[0].d.shape);
@@ -721,12 +751,7 @@ int shp_set_tiling(shp_plan p, int blk, int op, int strategy, int E, int NT, int
   t.E = E;
   t.NT = NT;
   t.persist = persistent;
-  if (blk >= 0)
-    p->blocks[blk].tiling[opk] = t;
-  else {
-    p->mixed[opk] = t;
-    p->mixed_dirty[opk] = true;
-  }
+  set_tiling_raw(p, blk, opk, t);
   return SHP_OK;
 }
 
@@ -751,15 +776,22 @@ int shp_get_tiling(shp_plan p, int blk, int op, int strategy, int* E, int* NT, i
   return SHP_OK;
 }
 
+// whether the matrix-core whole-mesh launch takes the plan's blocks
+static bool mf_mesh(shp_plan p) {
+  return p->uniform_P && !is_2d(p->blocks[0].d.shape) && (int)p->blocks.size() <= MF_MAX_BLK;
+}
+
 // Build and upload the whole-mesh tile list of one operator: tiles of E
 // elements from every block, heaviest first (longest-processing-time order).
 static Tiling mixed_tiling(shp_plan p, int opk) {
-  Tiling t = p->mixed[opk];
+  // the FP32 actions follow the FP64 action's launch shape when one is set
+  Tiling t = p->mixed[opk == OPK_HELM_F32 ? (int)OPK_HELM : opk == OPK_LAP_F32 ? (int)OPK_LAP : opk];
   if (t.E > 0 && t.NT > 0) return t;
   if (opk == OPK_HELM_ISO || opk == OPK_LAP_ISO) return iso_tiling(p->blocks[0].d.P);
   const int P0 = p->blocks[0].d.P;
   const bool dim2 = is_2d(p->blocks[0].d.shape);
-  if ((opk == OPK_HELM || opk == OPK_LAP || opk == OPK_ADR) && p->uniform_P && P0 >= 7 && !dim2) {
+  if (int E, NT; mf_action(opk) && mf_mesh(p) && mf_helm_shape(P0, &E, &NT)) return Tiling{E, NT, 2};
+  if (helm_action(opk) && p->uniform_P && P0 >= 7 && !dim2) {
     t.E = HI_MESH_E[P0 - 7];
     t.NT = HI_MESH_NT[P0 - 7];
     t.persist = 2;
@@ -767,10 +799,11 @@ static Tiling mixed_tiling(shp_plan p, int opk) {
   }
   t = Tiling{64, 512, 2};
   for (const auto& B : p->blocks) {
-    Tiling d = default_tiling(B.d.shape, B.d.P, opk);
+    // the thread-per-line tile's shape (that of the FP32 actions)
+    const int dk = helm_action(opk) ? (int)OPK_HELM_F32 : opk;
+    Tiling d = default_tiling(B.d.shape, B.d.P, dk);
     const long long Q3 = (long long)B.d.Q * B.d.Q * B.d.Q;
-    if ((opk == OPK_HELM || opk == OPK_LAP || opk == OPK_ADR) && !dim2 && d.E * Q3 <= 2LL * d.NT)
-      d = default_tiling(B.d.shape, B.d.P, opk, 64 * 1024);
+    if (helm_action(opk) && !dim2 && d.E * Q3 <= 2LL * d.NT) d = default_tiling(B.d.shape, B.d.P, dk, 64 * 1024);
     t.E = std::min(t.E, d.E);
     t.NT = std::min(t.NT, d.NT);
     t.persist = std::min(t.persist, d.persist);
@@ -896,6 +929,69 @@ static int resolve_auto(shp_plan p, int blk, int op, hipStream_t s, int* strateg
   }
   *strategy = B.auto_strategy[op];
   return SHP_OK;
+}
+
+// whether launch shape t of operator opk is the matrix-core launch's
+static bool mf_runs(int opk, int P, const Tiling& t) {
+  int E, NT;
+  return mf_action(opk) && t.persist == 2 && mf_helm_shape(P, &E, &NT) && t.E == E && t.NT == NT;
+}
+
+static MfBlock mf_block(shp_plan p, int blk, const double* in, double* out) {
+  const Block& B = p->blocks[blk];
+  MfBlock m{};
+  m.img = reinterpret_cast<const double*>(p->ws + B.off_mf);
+  m.fac = reinterpret_cast<const double*>(p->ws + B.off_fac);
+  m.in = in;
+  m.out = out;
+  m.n_elem = B.d.n_elem;
+  m.shape = B.d.shape;
+  return m;
+}
+
+// the matrix-core launch of operator opk over block blk (in/out its own buffers)
+// or, blk = -1, over every block, the costlier shapes first; adv: the advection
+// factors of OPK_ADR
+static hipError_t apply_mf(shp_plan p, int blk, int opk, const double* in, double* out, const double* adv,
+                           double lambda, hipStream_t s) {
+  MfMesh m{};
+  if (blk >= 0) {
+    m.blk[m.nblk++] = mf_block(p, blk, in, out);
+  } else {
+    int order[MF_MAX_BLK];
+    for (int b = 0; b < (int)p->blocks.size(); ++b) order[b] = b;
+    auto cost = [&](int b) { return LPT_WEIGHT[p->blocks[b].d.shape][p->blocks[b].d.P - 1]; };
+    std::stable_sort(order, order + p->blocks.size(), [&](int a, int b) { return cost(a) > cost(b); });
+    for (int i = 0; i < (int)p->blocks.size(); ++i) {
+      const Block& B = p->blocks[order[i]];
+      MfBlock& k = m.blk[m.nblk++];
+      k = mf_block(p, order[i], in + B.coeff_off, out + B.coeff_off);
+      if (adv) k.aux = adv + 3 * B.phys_off;
+    }
+  }
+  return launch_mf_helm(p->blocks[blk >= 0 ? blk : 0].d.P, m, lambda, opk != OPK_LAP, s);
+}
+
+// sum-factorised operator opk on block blk; in/out the block's buffers, cs the
+// component stride of vector fields
+static hipError_t apply_block(shp_plan p, int blk, int opk, const double* in, double* out, long long cs,
+                              double lambda, hipStream_t s) {
+  const Block& B = p->blocks[blk];
+  const Tiling t = effective(B.tiling[opk], B.d.shape, B.d.P, opk);
+  if (mf_runs(opk, B.d.P, t)) return apply_mf(p, blk, opk, in, out, nullptr, lambda, s);
+  OpArgs a{};
+  a.tab = reinterpret_cast<const double*>(p->ws + B.off_tab);
+  a.itab = reinterpret_cast<const int*>(p->ws + B.off_itab);
+  a.fac = reinterpret_cast<const double*>(p->ws + B.off_fac);
+  a.dxi = reinterpret_cast<const double*>(p->ws + B.off_dxi);
+  a.in = in;
+  a.out = out;
+  a.n_elem = B.d.n_elem;
+  a.in_cs = cs;
+  a.out_cs = cs;
+  a.lambda = lambda;
+  a.E = t.E;
+  return launch_block(B.d.shape, B.d.P, opk, a, t.NT, t.persist, s);
 }
 
 int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, double* out, double lambda, void* stream) {
@@ -1091,20 +1187,7 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
   if (blk >= 0) {
     Block& B = p->blocks[blk];
     if (needs_geom && !B.geom_ok) return fail(SHP_ERR_STATE, "block %d: geometry not set", blk);
-    const Tiling t = effective(B.tiling[opk], B.d.shape, B.d.P, opk);
-    OpArgs a{};
-    a.tab = reinterpret_cast<const double*>(p->ws + B.off_tab);
-    a.itab = reinterpret_cast<const int*>(p->ws + B.off_itab);
-    a.fac = reinterpret_cast<const double*>(p->ws + B.off_fac);
-    a.dxi = reinterpret_cast<const double*>(p->ws + B.off_dxi);
-    a.in = in;
-    a.out = out;
-    a.n_elem = B.d.n_elem;
-    a.in_cs = B.d.n_elem * (long long)B.NQ;
-    a.out_cs = a.in_cs;
-    a.lambda = lambda;
-    a.E = t.E;
-    hipError_t e = launch_block(B.d.shape, B.d.P, opk, a, t.NT, t.persist, s);
+    const hipError_t e = apply_block(p, blk, opk, in, out, B.d.n_elem * (long long)B.NQ, lambda, s);
     if (e != hipSuccess) return dev_fail(e, "operator launch");
     return SHP_OK;
   }
@@ -1117,28 +1200,20 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
       Block& B = p->blocks[b];
       const double* bin = in + (in_is_modes(opk) ? B.coeff_off : B.phys_off);
       double* bout = out + (out_is_modes(opk) ? B.coeff_off : B.phys_off);
-      const Tiling t = effective(B.tiling[opk], B.d.shape, B.d.P, opk);
-      OpArgs a{};
-      a.tab = reinterpret_cast<const double*>(p->ws + B.off_tab);
-      a.itab = reinterpret_cast<const int*>(p->ws + B.off_itab);
-      a.fac = reinterpret_cast<const double*>(p->ws + B.off_fac);
-      a.dxi = reinterpret_cast<const double*>(p->ws + B.off_dxi);
-      a.in = bin;
-      a.out = bout;
-      a.n_elem = B.d.n_elem;
-      a.in_cs = p->total_phys;
-      a.out_cs = p->total_phys;
-      a.lambda = lambda;
-      a.E = t.E;
-      hipError_t e = launch_block(B.d.shape, B.d.P, opk, a, t.NT, t.persist, s);
+      const hipError_t e = apply_block(p, (int)b, opk, bin, bout, p->total_phys, lambda, s);
       if (e != hipSuccess) return dev_fail(e, "operator launch");
     }
     return SHP_OK;
   }
-  if (p->mixed_dirty[opk])
-    if (int r = build_tiles(p, opk, s)) return r;
   const Tiling mt = mixed_tiling(p, opk);
   const int E = mt.E, NT = mt.NT;
+  if (mf_mesh(p) && mf_runs(opk, p->blocks[0].d.P, mt)) {
+    const hipError_t e = apply_mf(p, -1, opk, in, out, nullptr, lambda, s);
+    if (e != hipSuccess) return dev_fail(e, "mixed launch");
+    return SHP_OK;
+  }
+  if (p->mixed_dirty[opk])
+    if (int r = build_tiles(p, opk, s)) return r;
   size_t lds = 0;
   for (const auto& B : p->blocks) lds = std::max(lds, op_lds_bytes(B.d.shape, B.d.P, opk, E, mt.persist));
   const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
@@ -1269,17 +1344,18 @@ int shp_apply_prec(shp_plan p, int blk, int op, int strategy, int prec, const vo
     if (is_2d(p->blocks[b].d.shape)) return fail(SHP_ERR_UNSUPPORTED, "FP32 contractions cover the 3D shapes");
   }
   const int opk = (op == SHP_OP_HELMHOLTZ) ? OPK_HELM : OPK_LAP;
+  const int tk = (op == SHP_OP_HELMHOLTZ) ? OPK_HELM_F32 : OPK_LAP_F32;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (p->mixed_dirty[opk])
-    if (int r = build_tiles(p, opk, s)) return r;
-  const Tiling mt = mixed_tiling(p, opk);
+  if (p->mixed_dirty[tk])
+    if (int r = build_tiles(p, tk, s)) return r;
+  const Tiling mt = mixed_tiling(p, tk);
   size_t lds = 0;
   for (const auto& B : p->blocks) lds = std::max(lds, lds_bytes_f32(B.d.shape, B.d.P, mt.E));
   if (points_per_thread((long long)mt.E * (p->blocks[0].d.Q) * p->blocks[0].d.Q * p->blocks[0].d.Q, mt.NT) == 0)
     return fail(SHP_ERR_UNSUPPORTED, "launch shape too large for the FP32 kernel's register slots");
-  const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
+  const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)tk * p->max_tiles;
   hipError_t e = launch_mixed_f32(p->blocks[0].d.P, opk, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat),
-                                  tiles, p->mixed_ntiles[opk], static_cast<const float*>(in), static_cast<float*>(out),
+                                  tiles, p->mixed_ntiles[tk], static_cast<const float*>(in), static_cast<float*>(out),
                                   lambda, mt.NT, lds, mt.E, p->fac32 != nullptr, s);
   if (e != hipSuccess) return dev_fail(e, "FP32 launch");
   return SHP_OK;
@@ -1316,9 +1392,14 @@ int shp_apply_adr(shp_plan p, const double* adv, const double* in, double* out, 
       return fail(SHP_ERR_UNSUPPORTED, "the advection-diffusion-reaction action needs 3D blocks with precomputed factors");
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const Tiling mt = mixed_tiling(p, OPK_ADR);
+  if (mf_mesh(p) && mf_runs(OPK_ADR, p->blocks[0].d.P, mt)) {
+    const hipError_t e = apply_mf(p, -1, OPK_ADR, in, out, adv, lambda, s);
+    if (e != hipSuccess) return dev_fail(e, "advection-diffusion-reaction launch");
+    return SHP_OK;
+  }
   if (p->mixed_dirty[OPK_ADR])
     if (int r = build_tiles(p, OPK_ADR, s)) return r;
-  const Tiling mt = mixed_tiling(p, OPK_ADR);
   const int Q = p->blocks[0].d.Q;
   if (points_per_thread((long long)mt.E * Q * Q * Q, mt.NT) == 0)
     return fail(SHP_ERR_UNSUPPORTED, "launch shape too large for the advection-diffusion-reaction kernel");
@@ -1348,15 +1429,6 @@ static long long out_count(shp_plan p, int blk, int op) {
   if (op == SHP_OP_BWDTRANS) return pts;
   if (op == SHP_OP_PHYSDERIV) return 3 * pts;
   return modes;
-}
-
-static void set_tiling_raw(shp_plan p, int blk, int opk, const Tiling& t) {
-  if (blk >= 0)
-    p->blocks[blk].tiling[opk] = t;
-  else {
-    p->mixed[opk] = t;
-    p->mixed_dirty[opk] = true;
-  }
 }
 
 static Tiling get_tiling_raw(shp_plan p, int blk, int opk) {

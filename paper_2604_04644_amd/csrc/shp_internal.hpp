@@ -108,6 +108,33 @@ hipError_t launch_adr(int P, const BlockStatic* blocks, const Tile* tiles, int n
                       const double* adv, double lambda, int threads, size_t lds, int E, hipStream_t s);
 hipError_t launch_adv_factors(const double* fac, const double* dxi, const double* vel, long long vstride, double* adv,
                               long long n_elem, int Q3, hipStream_t s);
+// the FP64 sum-factorisation on the matrix cores (shp_kernels_mf.hpp): blocks of
+// one order P, in the order their work-groups run
+constexpr int MF_MAX_BLK = 16;
+struct MfBlock {
+  const double* img;  // table image (mf_layout)
+  const double* fac;
+  const double* aux;  // advection factors of the block, or null
+  const double* in;
+  double* out;
+  long long n_elem;
+  int shape;
+  int pad_;
+};
+struct MfMesh {
+  MfBlock blk[MF_MAX_BLK];
+  long long tile0[MF_MAX_BLK];  // tiles of the blocks before (set by the launcher)
+  int nblk;
+  int pad_;
+};
+// the table image of a shape
+void build_mf_image(int sh, int P, const std::vector<double>& tab, const std::vector<int>& itab,
+                    std::vector<double>& img);
+// elements per work-group and threads of the Laplacian / Helmholtz launch; false
+// for the orders that run faster on the thread-per-line tile
+bool mf_helm_shape(int P, int* E, int* NT);
+// react: with the reaction term lambda jw u (not for the Laplacian)
+hipError_t launch_mf_helm(int P, MfMesh& m, double lambda, bool react, hipStream_t s);
 hipError_t launch_mixed(int P, int opk, const BlockStatic* blocks, const Tile* tiles, int ntiles, const double* in,
                         double* out, long long in_cs, long long out_cs, double lambda, int threads, size_t lds, int E,
                         int persist, hipStream_t s);

@@ -100,6 +100,26 @@ constexpr TabLayout tab_layout(int sh, int P) {
   return t;
 }
 
+// The tables of the FP64 matrix-core stages as one image, copied to LDS by every
+// work-group: A1, B2, C3 (as above), zeros that the padded rows of C3 read, the
+// columns in family order (int: column + 256 x mode offset), then D with zeros
+// behind it.  Operators without derivatives copy the part before D.
+struct MfLayout {
+  int A, B, C, cols, D, total;  // D and total even, in doubles
+};
+constexpr MfLayout mf_layout(int sh, int P) {
+  const TabLayout t = tab_layout(sh, P);
+  const int pad = 4 * t.Q + 4;
+  MfLayout m{};
+  m.A = 0;
+  m.B = t.n * t.Q;
+  m.C = m.B + t.nb2 * t.Q;
+  m.cols = m.C + t.nc3 * t.Q + pad;
+  m.D = (m.cols + (num_cols(sh, P) + 1) / 2 + 1) / 2 * 2;
+  m.total = (m.D + 3 * t.Q * t.Q + pad + 1) / 2 * 2;
+  return m;
+}
+
 // Per-column integer table: (p, q, mode offset, run length, eta3 family base)
 constexpr int ICOL = 5;
 

@@ -10,6 +10,7 @@
 // Collocation derivative (Sec. 2.2, eq. dphitodh): barycentric form of the
 // derivative of the Lagrange interpolant, D_ij = (l_j / l_i) / (x_i - x_j),
 // D_ii = -sum_{j != i} D_ij.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -220,6 +221,25 @@ void build_tables(int sh, int P, int pts, std::vector<double>& tab, std::vector<
     }
   }
   fst[P + 1] = k;
+}
+
+void build_mf_image(int sh, int P, const std::vector<double>& tab, const std::vector<int>& itab,
+                    std::vector<double>& img) {
+  const TabLayout L = tab_layout(sh, P);
+  const MfLayout m = mf_layout(sh, P);
+  const int Q = L.Q, NC = num_cols(sh, P);
+  img.assign(m.total, 0.0);
+  std::copy_n(tab.begin() + L.A1, L.n * Q, img.begin() + m.A);
+  std::copy_n(tab.begin() + L.B2, L.nb2 * Q, img.begin() + m.B);
+  std::copy_n(tab.begin() + L.C3, L.nc3 * Q, img.begin() + m.C);
+  std::copy_n(tab.begin() + L.D, 3 * Q * Q, img.begin() + m.D);
+  std::vector<int> cols(NC);
+  const int* perm = itab.data() + NC * ICOL + (P + 2);
+  for (int t = 0; t < NC; ++t) {
+    const int c = sh == HEX ? t : perm[t];
+    cols[t] = c | (itab[c * ICOL + 2] << 8);
+  }
+  std::memcpy(img.data() + m.cols, cols.data(), sizeof(int) * NC);
 }
 
 // Dense reference matrices [B; d_1 B; d_2 B; d_3 B] at the quadrature points

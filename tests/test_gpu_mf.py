@@ -1,0 +1,82 @@
+"""The FP64 matrix-core launches against the thread-per-line tile and the oracle,
+at the edges of their tiles (elements per work-group) and block lists.
+
+Both launches do each element's sums in the same order with one rounding per
+step, so their results are equal bit for bit; the oracle's bar is the FP64
+operators' (1e-12 of the largest value).  Every case prints its name before it
+touches the GPU."""
+import numpy as np
+import pytest
+
+from oracle import shp_oracle as O
+from paper_2604_04644_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+
+
+@pytest.fixture(scope="module")
+def shp():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2604_04644_amd import shp as S
+    S.lib()
+    return S
+
+
+def rel(a, b):
+    return float(np.abs(a - b).max() / max(np.abs(b).max(), 1e-300))
+
+
+def plan_of(shp, blocks, P, pts="gj"):
+    """A plan of curved blocks [(shape, n)] and the oracle's Jacobians."""
+    plan = shp.Plan([(s, P, n, "curved", pts) for s, n in blocks])
+    jo = []
+    for b, (s, n) in enumerate(blocks):
+        maps = W.shape_batch(s, max(n, 1)).take(np.arange(n))
+        xi, _ = shp.quadrature(s, P + 2, pts)
+        plan.set_geometry(b, torch.from_numpy(W.jacobian(maps, xi, curved=True)).cuda())
+        jo.append(W.jacobian(maps, O.reference_points(s, P + 2, pts), curved=True))
+    return plan, jo
+
+
+@pytest.mark.parametrize("P,n", [(2, 1), (2, 8), (2, 17), (6, 1), (6, 3), (9, 2), (10, 1), (10, 3)])
+@pytest.mark.parametrize("shape", O.SHAPES)
+def test_helm_block(shp, shape, P, n):
+    """One block around the tile's element count, both point sets."""
+    for pts in ("gj", "radau"):
+        print(f"[mf] block {shape} P={P} n={n} {pts}", flush=True)
+        plan, jo = plan_of(shp, [(shape, n)], P, pts)
+        for op in ("helmholtz", "laplacian"):
+            x = W.coeffs(n, plan.n_modes[0], 20 + P)
+            xt = torch.from_numpy(x).cuda()
+            plan.set_tiling(0, op, 0, 0, 0)
+            y = plan.apply(0, op, xt, lam=0.8).cpu().numpy()
+            plan.set_tiling(0, op, 1, 64, 0)
+            assert np.array_equal(y, plan.apply(0, op, xt, lam=0.8).cpu().numpy()), op
+            ref = O.apply_op(op, shape, P, P + 2, jo[0], x, lam=0.8, pts=pts)
+            assert rel(y, ref) <= TOL, op
+
+
+@pytest.mark.parametrize("P", [2, 6, 10])
+@pytest.mark.parametrize("nblk", [3, 16, 17])
+def test_helm_mesh(shp, P, nblk):
+    """Whole-mesh launches over uneven and empty blocks, up to and past the number
+    of blocks that one matrix-core launch takes; with zero velocity the
+    advection-diffusion-reaction action is the Helmholtz action."""
+    print(f"[mf] mesh P={P} blocks={nblk}", flush=True)
+    blocks = [(O.SHAPES[(3 * b) % 4], (0 if b == 1 else 1 + (5 * b) % 11)) for b in range(nblk)]
+    plan, _ = plan_of(shp, blocks, P)
+    nc, npnt = plan.totals()
+    x = torch.from_numpy(W.coeffs(1, nc, 77)[0]).cuda()
+    adv = plan.advection_factors(torch.zeros(3, npnt, dtype=torch.float64, device="cuda"))
+    y = plan.apply(-1, "helmholtz", x, lam=1.1)
+    assert torch.equal(plan.apply_adr(x, adv, lam=1.1), y)
+    for b, (s, n) in enumerate(blocks):
+        if n:
+            co, _ = plan.offsets(b)
+            xb = x[co:co + n * plan.n_modes[b]].clone()
+            plan.set_tiling(b, "helmholtz", 1, 64, 0)
+            assert torch.equal(plan.apply(b, "helmholtz", xb, lam=1.1).reshape(-1), y[co:co + n * plan.n_modes[b]]), b
