@@ -70,7 +70,7 @@ struct Block {
   std::vector<float> tabf; // the reference tables rounded to FP32
   std::vector<double> dtab; // sum-factorised Helmholtz diagonal: 1D factor tables
   std::vector<int> ditab;   //   and their pair and mode indices
-  int dn1 = 0, dn12 = 0;
+  DiagDims dn;
   size_t off_dtab = 0, off_ditab = 0;
   std::vector<double> mf;   // table image of the matrix-core stages
   size_t off_mf = 0;
@@ -371,7 +371,7 @@ int shp_plan_create(shp_plan* out, const shp_block_desc* blk, int nblk) {
     B.NQ = B.d.Q * B.d.Q * B.d.Q;
     build_tables(B.d.shape, B.d.P, B.d.pts, B.tab, B.itab);
     build_mf_image(B.d.shape, B.d.P, B.tab, B.itab, B.mf);
-    build_diag_tables(B.d.shape, B.d.P, B.d.pts, B.dtab, B.ditab, B.dn1, B.dn12);
+    build_diag_tables(B.d.shape, B.d.P, B.d.pts, B.dtab, B.ditab, B.dn);
     if (B.iso()) build_ref_weights(B.d.shape, B.d.P, B.d.pts, B.wref);
     if (B.d.P <= LOCALMAT_MAX_P && !B.iso()) {
       int q3p, kp;
@@ -654,11 +654,22 @@ namespace shp {
 long long plan_total_coeff(const shp_plan_s* p) { return p ? p->total_coeff : 0; }
 
 int plan_helm_diag(shp_plan_s* p, double lambda, double* diag, hipStream_t s) {
-  for (const Block& B : p->blocks) {
-    const hipError_t e = launch_helm_diag(reinterpret_cast<const double*>(p->ws + B.off_fac),
-                                          reinterpret_cast<const double*>(p->ws + B.off_dtab),
-                                          reinterpret_cast<const int*>(p->ws + B.off_ditab), B.d.Q, B.dn1, B.dn12,
-                                          B.NP, B.d.n_elem, lambda, diag + B.coeff_off, s);
+  // one launch over as many neighbouring blocks of one order as it takes
+  for (size_t b = 0; b < p->blocks.size();) {
+    DiagMesh m{};
+    const int Q = p->blocks[b].d.Q;
+    for (; b < p->blocks.size() && m.nblk < DIAG_MAX_BLK && p->blocks[b].d.Q == Q; ++b) {
+      const Block& B = p->blocks[b];
+      DiagBlock& k = m.blk[m.nblk++];
+      k.fac = reinterpret_cast<const double*>(p->ws + B.off_fac);
+      k.dt = reinterpret_cast<const double*>(p->ws + B.off_dtab);
+      k.di = reinterpret_cast<const int*>(p->ws + B.off_ditab);
+      k.diag = diag + B.coeff_off;
+      k.n_elem = B.d.n_elem;
+      k.n = B.dn;
+      k.NP = B.NP;
+    }
+    const hipError_t e = launch_helm_diag(m, Q, lambda, s);
     if (e != hipSuccess) return dev_fail(e, "Helmholtz diagonal");
   }
   return SHP_OK;

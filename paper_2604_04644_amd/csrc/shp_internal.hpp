@@ -48,12 +48,32 @@ void build_localmat(int sh, int P, int pts, std::vector<double>& bcat, int& Q3p,
 // dense collocation derivative matrices of the tensor points, [3][Q3p][Q3p]
 // (d/d eta_d of the Lagrange interpolant; zero padding past Q^3)
 void build_dense_deriv(int sh, int P, int pts, std::vector<double>& dm, int& Q3p);
-// tables of the sum-factorised Helmholtz diagonal (see shp_tables.cpp)
-void build_diag_tables(int sh, int P, int pts, std::vector<double>& dt, std::vector<int>& di, int& n1, int& n12);
-// diag(lambda M + L) of n_elem elements of one block from its factors
-// fac [n_elem][NFAC][Q^3]: one work-group per element; diag [n_elem][NP]
-hipError_t launch_helm_diag(const double* fac, const double* dt, const int* di, int Q, int n1, int n12, int NP,
-                            long long n_elem, double lambda, double* diag, hipStream_t s);
+// tables of the sum-factorised Helmholtz diagonal (see shp_tables.cpp): numbers
+// of distinct factors per direction and of (eta1, eta2) pairs
+struct DiagDims {
+  int n1 = 0, n2 = 0, n3 = 0, n12 = 0;
+};
+void build_diag_tables(int sh, int P, int pts, std::vector<double>& dt, std::vector<int>& di, DiagDims& n);
+// diag(lambda M + L) of the elements of up to DIAG_MAX_BLK blocks with the same Q,
+// from their factors fac [n_elem][NFAC][Q^3]; diag [n_elem][NP] per block
+constexpr int DIAG_MAX_BLK = 8;
+struct DiagBlock {
+  const double* fac;
+  const double* dt;
+  const int* di;
+  double* diag;
+  long long n_elem;
+  long long wg0;  // work-groups of the blocks before (set by the launcher)
+  DiagDims n;
+  int NP;
+  int pad_;
+};
+struct DiagMesh {
+  DiagBlock blk[DIAG_MAX_BLK];
+  int nblk;
+  int per_wg;  // element groups per work-group (set by the launcher)
+};
+hipError_t launch_helm_diag(DiagMesh& m, int Q, double lambda, hipStream_t s);
 constexpr int LOCALMAT_MAX_P = 4;  // dense reference matrices only at low order
 // affine blocks: the 7 reference matrices of H = sum_k c_{e,k} A_k in MFMA
 // fragment order (Kp = modes padded to 16, 7 Kp^2 values); coefficients per element

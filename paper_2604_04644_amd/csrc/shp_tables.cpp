@@ -338,60 +338,46 @@ void build_localmat(int sh, int P, int pts, std::vector<double>& bcat, int& Q3p,
       }
 }
 
-// Tables of the sum-factorised Helmholtz diagonal.  The distinct eta1 factors
-// (rows), the distinct (eta1 row, eta2 factor) pairs and every mode's eta3
-// factor, each as values and derivatives at the direction's points:
-//   doubles: U1[n1][Q] W1[n1][Q] U2[n12][Q] W2[n12][Q] U3[NP][Q] W3[NP][Q]
-//   ints:    row of pair [n12], pair of mode [NP]
-void build_diag_tables(int sh, int P, int pts, std::vector<double>& dt, std::vector<int>& di, int& n1, int& n12) {
-  const int Q = P + 2, NP = num_modes(sh, P);
+// Tables of the sum-factorised Helmholtz diagonal: the distinct 1D factors of
+// each direction as the products u u, u w and w w of value and derivative at the
+// direction's points, and which of them make up the modes:
+//   doubles: T1[3][n1][Q] T2[3][n2][Q] T3[3][n3][Q]
+//   ints:    per distinct (eta1, eta2) pair, eta1 factor + 65536 x eta2 factor
+//            [n12]; per mode, pair + 65536 x eta3 factor [NP]
+void build_diag_tables(int sh, int P, int pts, std::vector<double>& dt, std::vector<int>& di, DiagDims& n) {
+  const int Q = P + 2;
   std::vector<double> z(3 * Q), w(3 * Q);
   for (int d = 0; d < 3; ++d) rule_1d(Q, alpha_dir(sh, d), pts, z.data() + d * Q, w.data() + d * Q);
-  std::vector<Factor> rows;
-  std::vector<std::pair<int, Factor>> pairs;
-  std::vector<int> mode_pair;
-  std::vector<Factor> mode_c;
+  std::vector<Factor> fac[3];
+  std::vector<int> pairs, modes;
+  auto find = [](auto& list, const auto& v) {
+    int i = 0;
+    while (i < (int)list.size() && !(list[i] == v)) ++i;
+    if (i == (int)list.size()) list.push_back(v);
+    return i;
+  };
   for (int p = 0; p <= P; ++p)
     for (int q = 0; q < nq_of(sh, P, p); ++q)
       for (int r = 0; r < col_len(sh, P, p, q); ++r) {
         Factor f[3];
         mode_factors(sh, p, q, r, f);
-        int ir = 0;
-        while (ir < (int)rows.size() && !(rows[ir] == f[0])) ++ir;
-        if (ir == (int)rows.size()) rows.push_back(f[0]);
-        int ip = 0;
-        while (ip < (int)pairs.size() && !(pairs[ip].first == ir && pairs[ip].second == f[1])) ++ip;
-        if (ip == (int)pairs.size()) pairs.push_back({ir, f[1]});
-        mode_pair.push_back(ip);
-        mode_c.push_back(f[2]);
+        const int i1 = find(fac[0], f[0]), i2 = find(fac[1], f[1]), i3 = find(fac[2], f[2]);
+        modes.push_back(find(pairs, i1 + 65536 * i2) + 65536 * i3);
       }
-  n1 = (int)rows.size();
-  n12 = (int)pairs.size();
-  dt.assign((size_t)2 * Q * (n1 + n12 + NP), 0.0);
-  double* U1 = dt.data();
-  double* W1 = U1 + n1 * Q;
-  double* U2 = W1 + n1 * Q;
-  double* W2 = U2 + n12 * Q;
-  double* U3 = W2 + n12 * Q;
-  double* W3 = U3 + NP * Q;
-  for (int a = 0; a < n1; ++a)
-    for (int i = 0; i < Q; ++i) {
-      U1[a * Q + i] = factor_value(rows[a], z[i], false);
-      W1[a * Q + i] = factor_value(rows[a], z[i], true);
-    }
-  for (int b = 0; b < n12; ++b)
-    for (int j = 0; j < Q; ++j) {
-      U2[b * Q + j] = factor_value(pairs[b].second, z[Q + j], false);
-      W2[b * Q + j] = factor_value(pairs[b].second, z[Q + j], true);
-    }
-  for (int m = 0; m < NP; ++m)
-    for (int k = 0; k < Q; ++k) {
-      U3[m * Q + k] = factor_value(mode_c[m], z[2 * Q + k], false);
-      W3[m * Q + k] = factor_value(mode_c[m], z[2 * Q + k], true);
-    }
-  di.assign(n12 + NP, 0);
-  for (int b = 0; b < n12; ++b) di[b] = pairs[b].first;
-  for (int m = 0; m < NP; ++m) di[n12 + m] = mode_pair[m];
+  n.n1 = (int)fac[0].size();
+  n.n2 = (int)fac[1].size();
+  n.n3 = (int)fac[2].size();
+  n.n12 = (int)pairs.size();
+  dt.clear();
+  for (int d = 0; d < 3; ++d)
+    for (int type = 0; type < 3; ++type)
+      for (const Factor& f : fac[d])
+        for (int i = 0; i < Q; ++i) {
+          const double u = factor_value(f, z[d * Q + i], false), v = factor_value(f, z[d * Q + i], true);
+          dt.push_back(type == 0 ? u * u : type == 1 ? u * v : v * v);
+        }
+  di = pairs;
+  di.insert(di.end(), modes.begin(), modes.end());
 }
 
 // d eta / d xi of the collapse at (e1, e2, e3), rows eta_d, columns xi_a, and
