@@ -29,7 +29,7 @@
 namespace {
 
 constexpr int NB = 1024;  // blocks of the dot-product reduction
-enum Slot { RZ = 0, PQ, RZN, RR, RR0, BB, RMAX, NSLOT };
+enum Slot { PQ = 0, RR, RR0, BB, RZ0, RZ1, BETA, NSLOT };
 
 template <typename T>
 __global__ void k_dot(const T* __restrict__ a, const T* __restrict__ b, long long n, double* __restrict__ part) {
@@ -46,8 +46,7 @@ __global__ void k_dot(const T* __restrict__ a, const T* __restrict__ b, long lon
   if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-// slot[dst] = sum of the partials; when dst == RZN also keep beta = RZN / RZ in
-// slot RMAX+1 and move RZN into RZ
+// slot[dst] = sum of the partials
 __global__ void k_dot_final(const double* __restrict__ part, int np, double* __restrict__ slot, int dst) {
   __shared__ double sh[256];
   double acc = 0.0;
@@ -58,13 +57,7 @@ __global__ void k_dot_final(const double* __restrict__ part, int np, double* __r
     if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    slot[dst] = sh[0];
-    if (dst == RZN) {
-      slot[NSLOT] = slot[RZ] > 0.0 ? sh[0] / slot[RZ] : 0.0;
-      slot[RZ] = sh[0];
-    }
-  }
+  if (threadIdx.x == 0) slot[dst] = sh[0];
 }
 
 // max |a| as the bit pattern of a non-negative double (ordered like an
@@ -83,7 +76,7 @@ __global__ void k_absmax(const double* __restrict__ a, long long n, unsigned lon
   if (threadIdx.x == 0) atomicMax(out, (unsigned long long)__double_as_longlong(sh[0]));
 }
 
-// r = b - y (FP64); rs = s r in the inner precision, s = 1 / max|r| from slot RMAX
+// r = b - y (FP64); rs = s r in the inner precision, s = 1 / max|r| from rmax
 template <typename T>
 __global__ void k_resid(const double* __restrict__ b, const double* __restrict__ y, double* __restrict__ r,
                         T* __restrict__ rs, const unsigned long long* __restrict__ rmax, long long n, int scale) {
@@ -132,24 +125,29 @@ __global__ void k_zero(T* __restrict__ a, long long n) {
     a[i] = (T)0;
 }
 
-// One pass for the vector work of a CG step: alpha = RZ / PQ, d += alpha p,
-// r -= alpha q, and the per-block partials of r^T z with z = r / diag (not
-// stored).  Launched on NB blocks of 256 threads, so element i goes to the same
-// thread, in the same order, as in k_dot: the partials equal k_dot's on (r, z).
-template <typename T>
-__global__ void k_cg1_rz(T* __restrict__ d, T* __restrict__ r, const T* __restrict__ p, const T* __restrict__ q,
-                         const T* __restrict__ dg, const double* __restrict__ slot, long long n,
-                         double* __restrict__ part) {
-  __shared__ double sh[256];
-  const T alpha = slot[PQ] > 0.0 ? (T)(slot[RZ] / slot[PQ]) : (T)0;  // 0 on breakdown, caught by the host check
-  double acc = 0.0;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-    d[i] += alpha * p[i];
-    const T ri = r[i] - alpha * q[i];
-    r[i] = ri;
-    const T zi = ri / dg[i];
-    acc = fma((double)ri, (double)zi, acc);
-  }
+// The sum of NB partials in k_dot_final's order, by every work-group (256
+// threads) that needs it, against a launch of its own (2.8 us and the gaps around
+// it).  All of a thread's loads are in flight together and every wave finishes
+// the sum by itself: one barrier (with a barrier per halving, 20 of them for two
+// sums, a launch that needed both took 4 us longer).
+__device__ __forceinline__ double sum_partials(const double* __restrict__ part, double* sh) {
+  double v[NB / 256], acc = 0.0;
+#pragma unroll
+  for (int i = 0; i < NB / 256; ++i) v[i] = part[threadIdx.x + 256 * i];
+#pragma unroll
+  for (int i = 0; i < NB / 256; ++i) acc += v[i];
+  sh[threadIdx.x] = acc;
+  __syncthreads();
+  const int l = threadIdx.x & 63;
+  double s = (sh[l] + sh[l + 128]) + (sh[l + 64] + sh[l + 192]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
+  s = __shfl(s, 0);
+  __syncthreads();  // sh is free again
+  return s;
+}
+// the work-group's sum of acc to part[blockIdx.x]
+__device__ __forceinline__ void store_partial(double acc, double* __restrict__ part, double* sh) {
   sh[threadIdx.x] = acc;
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) {
@@ -159,14 +157,72 @@ __global__ void k_cg1_rz(T* __restrict__ d, T* __restrict__ r, const T* __restri
   if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-// p = z + beta p (beta in slot NSLOT) with z = r / diag recomputed, rounded as
-// in k_jacobi
+// partials of r^T z, z = r / diag (rounded as in k_jacobi, not stored)
 template <typename T>
-__global__ void k_cg2_r(T* __restrict__ p, const T* __restrict__ r, const T* __restrict__ dg,
-                        const double* __restrict__ slot, long long n) {
-  const T beta = (T)slot[NSLOT];
+__global__ void __launch_bounds__(256) k_rz(const T* __restrict__ r, const T* __restrict__ dg, long long n,
+                                            double* __restrict__ part) {
+  __shared__ double sh[256];
+  double acc = 0.0;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+    const T ri = r[i];
+    const T zi = ri / dg[i];
+    acc = fma((double)ri, (double)zi, acc);
+  }
+  store_partial(acc, part, sh);
+}
+
+// One pass for the vector work of a CG step: alpha = RZ / PQ, d += alpha p,
+// r -= alpha q, and the per-block partials of the new r^T z (z = r / diag, not
+// stored).  RZ is in its slot, PQ the sum of the partials pq; it also goes to its
+// slot for the host's check.  Launched on NB blocks of 256 threads, so element i
+// goes to the same thread, in the same order, as in k_dot.
+template <typename T>
+__global__ void __launch_bounds__(256) k_cg1_rz(T* __restrict__ d, T* __restrict__ r, const T* __restrict__ p,
+                                                const T* __restrict__ q, const T* __restrict__ dg,
+                                                const double* __restrict__ pq, long long n, double* __restrict__ slot,
+                                                int rz, double* __restrict__ part) {
+  __shared__ double sh[256];
+  const double vpq = sum_partials(pq, sh);
+  if (blockIdx.x == 0 && threadIdx.x == 0) slot[PQ] = vpq;
+  const T alpha = vpq > 0.0 ? (T)(slot[rz] / vpq) : (T)0;  // 0 on breakdown, caught by the host check
+  double acc = 0.0;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+    d[i] += alpha * p[i];
+    const T ri = r[i] - alpha * q[i];
+    r[i] = ri;
+    const T zi = ri / dg[i];
+    acc = fma((double)ri, (double)zi, acc);
+  }
+  store_partial(acc, part, sh);
+}
+
+// RZ = r^T z from its partials into slot rz, and beta = RZ / (the step before's, in
+// the other slot) into slot BETA (first: no step before, 0)
+__device__ __forceinline__ double step_beta(const double* __restrict__ part, double* __restrict__ slot, int rz,
+                                            int first, double* sh) {
+  const double v = sum_partials(part, sh), old = slot[RZ0 + RZ1 - rz];
+  const double beta = !first && old > 0.0 ? v / old : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    slot[rz] = v;
+    slot[BETA] = beta;
+  }
+  return beta;
+}
+// the next search direction z + beta p, z = r / diag; first: z
+template <typename T>
+__device__ __forceinline__ T next_p(T r, T dg, T beta, const T* p, int first) {
+  return first ? r / dg : r / dg + beta * *p;
+}
+
+// p = z + beta p with z recomputed, rounded as in k_jacobi
+template <typename T>
+__global__ void __launch_bounds__(256) k_cg2_r(T* __restrict__ p, const T* __restrict__ r, const T* __restrict__ dg,
+                                               const double* __restrict__ part, double* __restrict__ slot, int rz,
+                                               int first, long long n) {
+  __shared__ double sh[256];
+  const T beta = (T)step_beta(part, slot, rz, first, sh);
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    p[i] = r[i] / dg[i] + beta * p[i];
+    p[i] = next_p(r[i], dg[i], beta, p + i, first);
 }
 
 __global__ void k_to_float(const double* __restrict__ a, float* __restrict__ b, long long n) {
@@ -207,14 +263,70 @@ __global__ void k_c0_scatter(const int64_t* __restrict__ row_ptr, const int64_t*
   }
 }
 
+// The assembled operator's CG step.  The next search direction p' = z + beta p is
+// formed where it is used: k_c0_gather_p gives each local coefficient its copy,
+// k_c0_scatter_dot forms it again per global DOF, stores it, sums the local copies
+// of q and takes the partials of p'^T q (the update of p, the dot product and its
+// final sum as kernels of their own made 8 launches of a step where 4 do).
+template <typename T>
+__global__ void __launch_bounds__(256) k_c0_gather_p(const int64_t* __restrict__ l2g, long long n_local,
+                                                     const T* __restrict__ r, const T* __restrict__ dg,
+                                                     const T* __restrict__ p, const double* __restrict__ part,
+                                                     double* __restrict__ slot, int rz, int first,
+                                                     T* __restrict__ xl) {
+  __shared__ double sh[256];
+  const T beta = (T)step_beta(part, slot, rz, first, sh);
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n_local;
+       i += (long long)gridDim.x * blockDim.x) {
+    const int64_t g = l2g[i];
+    T v = (T)0;
+    if (g != -1) {
+      const int64_t k = g >= 0 ? g : -2 - g;
+      v = next_p(r[k], dg[k], beta, p + k, first);
+      if (g < 0) v = -v;
+    }
+    xl[i] = v;
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_c0_scatter_dot(const int64_t* __restrict__ row_ptr,
+                                                        const int64_t* __restrict__ col, long long n_global,
+                                                        const T* __restrict__ yl, const T* __restrict__ r,
+                                                        const T* __restrict__ dg, const T* __restrict__ p,
+                                                        const double* __restrict__ slot, int first,
+                                                        T* __restrict__ p_new, T* __restrict__ q,
+                                                        double* __restrict__ part) {
+  __shared__ double sh[256];
+  const T beta = (T)slot[BETA];
+  double dot = 0.0;
+  for (long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x; g < n_global;
+       g += (long long)gridDim.x * blockDim.x) {
+    const T pn = next_p(r[g], dg[g], beta, p + g, first);
+    T acc = 0;
+    const int64_t j1 = row_ptr[g + 1];
+    for (int64_t j = row_ptr[g]; j < j1; ++j) {
+      const int64_t c = col[j];
+      acc += c >= 0 ? yl[c] : -yl[-1 - c];
+    }
+    q[g] = acc;
+    p_new[g] = pn;
+    dot = fma((double)pn, (double)acc, dot);
+  }
+  store_partial(dot, part, sh);
+}
+
+// launches whose work-groups each sum the partials first: what the chip holds at
+// once (8 work-groups of 256 on each of 256 CUs), not more
+inline dim3 grid_once(long long n) { return dim3((unsigned)std::min<long long>((n + 255) / 256, 2048)); }
 inline dim3 grid_for(long long n) { return dim3((unsigned)std::min<long long>((n + 255) / 256, 8192)); }
 
 int sfail(int code, const char* msg) { return shp::set_error(code, msg); }
 
 struct SolveWs {
-  double *r, *y, *xb, *slot, *part, *part_rz;  // part_rz: r^T z partials of k_cg1_rz
+  double *r, *y, *xb, *slot, *part, *rz, *pq;  // rz, pq: partials of r^T z and p^T q
   float* diagf;
-  void* vec;  // inner vectors: rs, z, p, q, d (5 n of the inner type)
+  void* vec;  // inner vectors: rs, p, another p, q, d (5 n of the inner type)
   unsigned long long* rmax;
 };
 
@@ -236,7 +348,8 @@ size_t carve(void* base, long long n, SolveWs* w) {
   s.vec = take(sizeof(double) * 5 * n);
   s.slot = reinterpret_cast<double*>(take(sizeof(double) * 16));
   s.part = reinterpret_cast<double*>(take(sizeof(double) * NB));
-  s.part_rz = reinterpret_cast<double*>(take(sizeof(double) * NB));
+  s.rz = reinterpret_cast<double*>(take(sizeof(double) * NB));
+  s.pq = reinterpret_cast<double*>(take(sizeof(double) * NB));
   s.rmax = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long) * 2));
   if (w) *w = s;
   return o;
@@ -279,9 +392,17 @@ struct ElemOp {
   int apply64(const double* x, double* y, hipStream_t s) const {
     return shp_apply(plan, -1, SHP_OP_HELMHOLTZ, SHP_AUTO, x, y, lambda, s);
   }
+  // One CG step up to q = H p and the partials of p^T q, with the search
+  // direction p' = z + beta p (first: z) of the residual r, whose r^T z goes to
+  // slot rz.  p: the old direction on entry and the new one on return (p2: room
+  // for another).
   template <typename T>
-  int apply(const T* x, T* y, hipStream_t s) const {
-    return apply_inner<T>(plan, x, y, lambda, prec, s);
+  int step(const T* r, const T* dg, T*& p, T*&, T* q, long long n, SolveWs& w, int rz, int first,
+           hipStream_t s) const {
+    hipLaunchKernelGGL(k_cg2_r<T>, grid_once(n), dim3(256), 0, s, p, r, dg, w.rz, w.slot, rz, first, n);
+    if (int e = apply_inner<T>(plan, p, q, lambda, prec, s)) return e;
+    hipLaunchKernelGGL(k_dot<T>, dim3(NB), dim3(256), 0, s, p, q, n, w.pq);
+    return hipGetLastError() == hipSuccess ? SHP_OK : SHP_ERR_DEVICE;
   }
 };
 
@@ -302,11 +423,20 @@ struct C0Op {
   }
   int apply64(const double* x, double* y, hipStream_t s) const { return run<double>(x, y, xl, yl, s); }
   template <typename T>
-  int apply(const T* x, T* y, hipStream_t s) const {
+  int step(const T* r, const T* dg, T*& p, T*& p2, T* q, long long, SolveWs& w, int rz, int first,
+           hipStream_t s) const {
+    T *xl_, *yl_;
     if constexpr (sizeof(T) == sizeof(float))
-      return run<float>(x, y, xlf, ylf, s);
+      xl_ = xlf, yl_ = ylf;
     else
-      return run<double>(x, y, xl, yl, s);
+      xl_ = xl, yl_ = yl;
+    hipLaunchKernelGGL(k_c0_gather_p<T>, grid_once(n_local), dim3(256), 0, s, l2g, n_local, r, dg, p, w.rz, w.slot, rz,
+                       first, xl_);
+    if (int e = apply_inner<T>(plan, xl_, yl_, lambda, prec, s)) return e;
+    hipLaunchKernelGGL(k_c0_scatter_dot<T>, dim3(NB), dim3(256), 0, s, row_ptr, col, n_global, yl_, r, dg, p, w.slot,
+                       first, p2, q, w.pq);
+    std::swap(p, p2);
+    return hipGetLastError() == hipSuccess ? SHP_OK : SHP_ERR_DEVICE;
   }
 };
 
@@ -332,12 +462,12 @@ template <typename T, typename Op>
 int pcg_reliable(const Op& op, const double* b, double* x, long long n, SolveWs& w, const T* dg, double tol,
                  int max_updates, int max_iter, double delta, double bnorm2, shp_solve_stats* st, hipStream_t s) {
   T* rs = static_cast<T*>(w.vec);
-  T* z = rs + n;
-  T* p = z + n;
-  T* q = p + n;
+  T* p = rs + n;
+  T* p2 = p + n;
+  T* q = p2 + n;
   T* d = q + n;
   const dim3 g = grid_for(n), bl(256);
-  double h[NSLOT + 1];
+  double h[NSLOT];
   auto readback = [&]() {
     return hipMemcpyAsync(h, w.slot, sizeof h, hipMemcpyDeviceToHost, s) == hipSuccess &&
            hipStreamSynchronize(s) == hipSuccess;
@@ -348,9 +478,7 @@ int pcg_reliable(const Op& op, const double* b, double* x, long long n, SolveWs&
   hipLaunchKernelGGL(k_absmax, dim3(NB), bl, 0, s, w.r, n, w.rmax);
   hipLaunchKernelGGL(k_resid<T>, g, bl, 0, s, b, w.y, w.r, rs, w.rmax, n, 1);
   hipLaunchKernelGGL(k_zero<T>, g, bl, 0, s, d, n);
-  hipLaunchKernelGGL(k_jacobi<T>, g, bl, 0, s, rs, dg, z, n);
-  hipLaunchKernelGGL(k_copy<T>, g, bl, 0, s, z, p, n);
-  if (int r = dot(rs, z, n, w, RZ, s)) return r;
+  hipLaunchKernelGGL(k_rz<T>, dim3(NB), bl, 0, s, rs, dg, n, w.rz);
   if (int r = dot(rs, rs, n, w, RR0, s)) return r;
   if (!readback()) return sfail(SHP_ERR_DEVICE, "solver readback");
   double rr_ref = h[RR0];
@@ -365,12 +493,14 @@ int pcg_reliable(const Op& op, const double* b, double* x, long long n, SolveWs&
   double best = st->rel_residual;
   int stalls = 0, last = 0;
   constexpr int MAX_GAP = 2000;  // iterations between updates at most
+  bool first = true;  // no direction to go on from
   for (int it = 1; it <= max_iter; ++it) {
-    if (int r = op.template apply<T>(p, q, s)) return r;
-    if (int r = dot(p, q, n, w, PQ, s)) return r;
-    hipLaunchKernelGGL(k_cg1_rz<T>, dim3(NB), bl, 0, s, d, rs, p, q, dg, w.slot, n, w.part_rz);
+    const int rz = it & 1 ? RZ0 : RZ1;  // r^T z of this step, that of the step before in the other
+    if (int r = op.template step<T>(rs, dg, p, p2, q, n, w, rz, first ? 1 : 0, s)) return r;
+    first = false;
+    hipLaunchKernelGGL(k_cg1_rz<T>, dim3(NB), bl, 0, s, d, rs, p, q, dg, w.pq, n, w.slot, rz, w.rz);
     st->inner_iters = it;
-    bool fresh_rz = true;  // part_rz holds r^T z of the current rs
+    bool fresh_rz = true;  // w.rz holds r^T z of the current rs
     if (it % 10 == 0 || it == max_iter) {
       if (int r = dot(rs, rs, n, w, RR, s)) return r;
       if (!readback()) return sfail(SHP_ERR_DEVICE, "solver readback");
@@ -413,21 +543,10 @@ int pcg_reliable(const Op& op, const double* b, double* x, long long n, SolveWs&
           if (++stalls >= 5) break;  // the residual floor of the FP64 action
         }
         if (st->outer_iters >= max_updates) break;
-        if (restart) {
-          hipLaunchKernelGGL(k_jacobi<T>, g, bl, 0, s, rs, dg, z, n);
-          hipLaunchKernelGGL(k_copy<T>, g, bl, 0, s, z, p, n);
-          if (int r = dot(rs, z, n, w, RZ, s)) return r;
-          continue;
-        }
+        first = restart;
       }
     }
-    if (fresh_rz) {
-      hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(256), 0, s, w.part_rz, NB, w.slot, (int)RZN);
-    } else {
-      hipLaunchKernelGGL(k_jacobi<T>, g, bl, 0, s, rs, dg, z, n);
-      if (int r = dot(rs, z, n, w, RZN, s)) return r;
-    }
-    hipLaunchKernelGGL(k_cg2_r<T>, g, bl, 0, s, p, rs, dg, w.slot, n);
+    if (!fresh_rz) hipLaunchKernelGGL(k_rz<T>, dim3(NB), bl, 0, s, rs, dg, n, w.rz);
   }
   return sfail(SHP_ERR_NOT_CONVERGED, "the residual did not reach the tolerance (x is the best iterate)");
 }
@@ -452,7 +571,7 @@ int solve_with(const Op& op, long long n, SolveWs& w, const double* diag, const 
   if (int r = (f32_vectors(inner_prec) ? true_residual<float>(op, b, x, n, w, false, s)
                                       : true_residual<double>(op, b, x, n, w, false, s)))
     return r;
-  double hs[NSLOT + 1];
+  double hs[NSLOT];
   if (hipMemcpyAsync(hs, w.slot, sizeof hs, hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return sfail(SHP_ERR_DEVICE, "solver readback");
