@@ -204,11 +204,21 @@ Tiling default_tiling(int sh, int P, int opk, size_t lds_budget = 40 * 1024) {
     t.persist = 0;
     return t;
   }
-  if (opk == OPK_BWD || opk == OPK_IPR || opk == OPK_DERIV || opk == OPK_IPRD || opk == OPK_MASS) {
-    // the plain collocated tile is bound by the latency of its staged line
-    // stages: about 1500 points per work-group, 512 threads from 768 points
-    // (the tuner's choices for these operators on the 32^3-cell mixed mesh
-    // at P = 2, 4, 6 were 640-960, 1512 and 2048 points)
+  if (values_op(opk)) {
+    // one eta1 line per thread: as many elements as 256 threads take, 512 from
+    // P = 9, where 256 hold two and one (of 29 shapes swept per operator and order
+    // on the mixed mesh the fastest or within 3 % of it; twice the elements on the
+    // same threads costs 5-30 %, half as many threads 0-20 %; P = 9 mass 2 / 256
+    // 56 us, 4 / 512 54; P = 10 1 / 256 70 us, 3 / 512 63)
+    t.NT = P >= 9 ? 512 : 256;
+    t.E = std::max(1, std::min(64, t.NT / ((P + 2) * (P + 2))));
+    t.persist = 0;
+    return t;
+  }
+  if (opk == OPK_DERIV || opk == OPK_IPRD) {
+    // the plain collocated tile: about 1500 points per work-group, 512 threads
+    // from 768 points (the tuner's choices on the 32^3-cell mixed mesh at
+    // P = 2, 4, 6 were 640-960, 1512 and 2048 points)
     int E = std::max(1, std::min(12, (int)((1536 + Q3 / 2) / Q3)));
     while (E > 1 && op_lds_bytes(sh, P, opk, E, 2) > 64 * 1024) --E;
     t.E = E;
@@ -243,9 +253,20 @@ Tiling iso_tiling(int P) {
   return t;
 }
 
-Tiling effective(const Tiling& set, int sh, int P, int opk) {
+// A launch of n_elem elements with fewer tiles than the chip has CUs takes smaller
+// ones (the transforms and the mass, whose tiles hold the most elements: 116
+// elements at P = 10, bwd + iprod + mass 34.8 us with 3 per work-group, 31 with 1).
+Tiling spread(Tiling t, long long n_elem, int opk) {
+  constexpr int CUS = 256;
+  if (values_op(opk) && n_elem < (long long)CUS * t.E) t.E = (int)std::max<long long>(1, (n_elem + CUS - 1) / CUS);
+  return t;
+}
+
+Tiling effective(const Tiling& set, int sh, int P, int opk, long long n_elem) {
   if (opk == OPK_HELM_ISO || opk == OPK_LAP_ISO) return iso_tiling(P);
-  return (set.E > 0 && set.NT > 0) ? set : default_tiling(sh, P, opk);
+  if (set.E > 0 && set.NT > 0) return set;
+  const Tiling t = default_tiling(sh, P, opk);
+  return is_2d(sh) ? t : spread(t, n_elem, opk);
 }
 
 int check_plan(shp_plan p) {
@@ -777,7 +798,7 @@ int shp_get_tiling(shp_plan p, int blk, int op, int strategy, int* E, int* NT, i
   Tiling t;
   if (blk >= 0) {
     const Block& B = p->blocks[blk];
-    t = effective(B.tiling[opk], B.d.shape, B.d.P, opk);
+    t = effective(B.tiling[opk], B.d.shape, B.d.P, opk, B.d.n_elem);
   } else {
     t = mixed_tiling(p, opk);
   }
@@ -819,7 +840,7 @@ static Tiling mixed_tiling(shp_plan p, int opk) {
     t.NT = std::min(t.NT, d.NT);
     t.persist = std::min(t.persist, d.persist);
   }
-  return t;
+  return dim2 ? t : spread(t, p->total_elem, opk);
 }
 
 // Relative cost of one element by shape (hex, prism, pyramid, tet) and
@@ -988,7 +1009,7 @@ static hipError_t apply_mf(shp_plan p, int blk, int opk, const double* in, doubl
 static hipError_t apply_block(shp_plan p, int blk, int opk, const double* in, double* out, long long cs,
                               double lambda, hipStream_t s) {
   const Block& B = p->blocks[blk];
-  const Tiling t = effective(B.tiling[opk], B.d.shape, B.d.P, opk);
+  const Tiling t = effective(B.tiling[opk], B.d.shape, B.d.P, opk, B.d.n_elem);
   if (mf_runs(opk, B.d.P, t)) return apply_mf(p, blk, opk, in, out, nullptr, lambda, s);
   OpArgs a{};
   a.tab = reinterpret_cast<const double*>(p->ws + B.off_tab);
@@ -1056,7 +1077,7 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
     if (blk >= 0 || !p->uniform_P) {
       for (int b = b0; b < b1 && e == hipSuccess; ++b) {
         const Block& B = p->blocks[b];
-        const Tiling t = effective(B.tiling[opk], B.d.shape, B.d.P, opk);
+        const Tiling t = effective(B.tiling[opk], B.d.shape, B.d.P, opk, B.d.n_elem);
         OpArgs a{};
         a.tab = reinterpret_cast<const double*>(p->ws + B.off_tab);
         a.fac = reinterpret_cast<const double*>(p->ws + B.off_fac);

@@ -242,7 +242,8 @@ size_t op_lds_bytes(int sh, int P, int opk, int E, int variant) {
   // 1 and 2, advection-diffusion-reaction, iso-parametric), whose LDS head
   // holds only the tables it reads per lane
   const bool helm = opk == OPK_HELM || opk == OPK_LAP || opk == OPK_ADR;
-  const int nbuf = (opk == OPK_HELM_NC || opk == OPK_LAP_NC) ? 5
+  const int nbuf = values_op(opk) ? 2
+                   : (opk == OPK_HELM_NC || opk == OPK_LAP_NC) ? 5
                    : (variant >= 3 && helm) ? 3
                    : (helm && (variant == 1 || variant == 2)) ? 0 : 4;
   switch (sh) {

@@ -128,8 +128,9 @@ struct Tile_ {
   ctab<R> ct;  // the same tables in global memory, for lane-uniform reads
   R* el;       // E * per
   int per;     // values per element: 4 buffers (U, G0, G1, G2), 3 fused, 5 non-collocated
+  int bs = D::S3;  // values from a buffer to the next (a whole point buffer but for the values tile)
   __device__ R* U(int e) const { return el + e * per; }
-  __device__ R* G(int e, int d) const { return el + e * per + (d + 1) * D::S3; }
+  __device__ R* G(int e, int d) const { return el + e * per + (d + 1) * bs; }
 };
 
 __device__ __forceinline__ int tid() { return threadIdx.x; }
@@ -792,66 +793,129 @@ __device__ void ipr_chain(const Tile_<SH, P, R>& T, int ne, int mask) {
   __syncthreads();
 }
 
-// The tile of every collocated operator: the stages read their tables through
+// The backward transform, the inner product and the mass.  The eta1 lines
+// (e, j, k) never leave the registers: stage p, the weights and stage p^T are one
+// task per line, so the tile holds the columns F and the rows G[p][j][k] only
+// (P = 4: 2.6 KB per element in place of the 6.9 KB of four point buffers), and
+// points are read and written straight from global memory, consecutive lanes on
+// consecutive points (j, k).  With the points staged through LDS the launches
+// waited on 5, 6 and 9 barriers instead of 3, 4 and 6 and reached a third of the
+// copy rate.  U holds the modes, the rows G and the result's modes, G(e, 0) the columns.
+template <int SH, int P>
+constexpr int values_bs() {
+  using D = Dims<SH, P>;
+  return imax(D::NP, D::n * D::Q * D::QP);
+}
+template <int SH, int P>
+constexpr int values_per() {
+  using D = Dims<SH, P>;
+  return values_bs<SH, P>() + D::NC * D::QP;
+}
+
+template <int SH, int P, int OP, typename R>
+__device__ void values_tile(const OpArgs& a, long long e0, int ne, const Tile_<SH, P, R>& T) {
+  using D = Dims<SH, P>;
+  constexpr int Q = D::Q, n = D::n, Q2 = D::Q2, Q3 = D::Q3, QP = D::QP;
+  constexpr bool weighted = OP != OPK_BWD;
+  load_tables_helm<SH, P>(a, T);
+  const double* fac = a.fac + e0 * (long long)(NFAC * Q3);
+  const R* src = reinterpret_cast<const R*>(a.in) + e0 * Q3;
+  // the weights (and values) of a thread's first line, loaded at the start so that
+  // they arrive during the stages before
+  double w[Q];
+  R u[Q];
+  const int nl = ne * Q2;
+  if constexpr (weighted) {
+    const int t = tid() < nl ? tid() : nl - 1;
+    const int e = t / Q2, jk = t - e * Q2;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) w[i] = fac[e * (NFAC * Q3) + i * Q2 + jk];
+    if constexpr (OP == OPK_IPR) {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) u[i] = src[e * Q3 + i * Q2 + jk];
+    }
+  }
+  if constexpr (OP != OPK_IPR) {
+    load_modes<SH, P>(T, reinterpret_cast<const R*>(a.in), e0, ne, -1);
+    __syncthreads();
+    bwd_r<SH, P, false>(T, ne, -1, 0);
+    __syncthreads();
+    bwd_q<SH, P, false>(T, ne, 0, -1);
+    __syncthreads();
+  }
+  for (int t = tid(); t < nl; t += nthr()) {
+    const int e = t / Q2, jk = t - e * Q2;
+    const int j = jk / Q, k = jk - j * Q;
+    R* G = T.U(e) + j * QP + k;
+    if constexpr (weighted) {
+      if (t != tid()) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) w[i] = fac[e * (NFAC * Q3) + i * Q2 + jk];
+        if constexpr (OP == OPK_IPR) {
+#pragma unroll
+          for (int i = 0; i < Q; ++i) u[i] = src[e * Q3 + i * Q2 + jk];
+        }
+      }
+    }
+    if constexpr (OP != OPK_IPR) {
+      const ctab<R> A1 = launder(T.ct) + D::L.A1;
+      R g[n];
+#pragma unroll
+      for (int p = 0; p < n; ++p) g[p] = G[p * Q * QP];
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        R s = 0.0;
+#pragma unroll
+        for (int p = 0; p < n; ++p) s = fma(A1[p * Q + i], g[p], s);
+        u[i] = s;
+      }
+    }
+    if constexpr (OP == OPK_BWD) {
+      R* dst = reinterpret_cast<R*>(a.out) + (e0 + e) * Q3 + jk;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) dst[i * Q2] = u[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) u[i] = w[i] * u[i];
+      const ctab<R> A1 = launder(T.ct) + D::L.A1;
+#pragma unroll
+      for (int p = 0; p < n; ++p) {
+        R s = 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) s = fma(A1[p * Q + i], u[i], s);
+        G[p * Q * QP] = s;
+      }
+    }
+  }
+  if constexpr (weighted) {
+    __syncthreads();
+    ipr_q<SH, P, false>(T, ne, -1, 0);
+    __syncthreads();
+    ipr_r<SH, P, false>(T, ne, 0, -1, false);
+    __syncthreads();
+    store_modes<SH, P>(T, reinterpret_cast<R*>(a.out), e0, ne, -1);
+  }
+}
+constexpr bool values_op(int op) { return op == OPK_BWD || op == OPK_IPR || op == OPK_MASS; }
+
+// The tile of the other collocated operators: the stages read their tables through
 // the constant path except the tet's eta2 table and the column table, which
 // are all the (compact) LDS head holds.
 template <int SH, int P, int OP, typename R>
 __device__ void tile_body(const OpArgs& a, long long e0, int ne, const Tile_<SH, P, R>& T) {
   using D = Dims<SH, P>;
   constexpr int Q3 = D::Q3;
-  load_tables_helm<SH, P>(a, T);
-  // the mass's jw at a thread's first PF points, loaded at the start so that
-  // the loads overlap the line stages (points past PF nthr() are read where
-  // they are used; prefetching the 9 d eta/d x of the physical derivative the
-  // same way costs it occupancy and time)
-  constexpr int PF = 4;
-  double gpf[PF];
-  if constexpr (OP == OPK_MASS) {
-    const double* g = a.fac + e0 * (long long)(NFAC * Q3);
-#pragma unroll
-    for (int it = 0; it < PF; ++it) {
-      const int t = tid() + it * nthr();
-      const int tc = t < ne * Q3 ? t : 0;  // in bounds; unused when t is past the tile
-      const int e = tc / Q3, pt = tc - e * Q3;
-      gpf[it] = g[e * (NFAC * Q3) + pt];
-    }
+  if constexpr (values_op(OP)) {
+    values_tile<SH, P, OP>(a, e0, ne, T);
+    return;
   }
-  if (OP == OPK_BWD || OP == OPK_MASS || OP == OPK_LAP || OP == OPK_HELM) {
+  load_tables_helm<SH, P>(a, T);
+  if (OP == OPK_LAP || OP == OPK_HELM) {
     load_modes<SH, P>(T, reinterpret_cast<const R*>(a.in), e0, ne, 0);
     __syncthreads();
     bwd_chain<SH, P>(T, ne);
   } else {
     __syncthreads();
-  }
-
-  if (OP == OPK_BWD) {
-    R* dst = reinterpret_cast<R*>(a.out) + e0 * Q3;
-    for (int t = tid(); t < ne * Q3; t += nthr()) {
-      const int e = t / Q3, pt = t - e * Q3;
-      dst[t] = T.U(e)[lds_pt<SH, P>(pt)];
-    }
-    return;
-  }
-
-  if (OP == OPK_IPR || OP == OPK_MASS) {
-    const double* fac = a.fac + e0 * (long long)(NFAC * Q3);
-    const R* src = reinterpret_cast<const R*>(a.in) + e0 * Q3;
-    int it = 0;
-    for (int t = tid(); t < ne * Q3; t += nthr(), ++it) {
-      const int e = t / Q3, pt = t - e * Q3;
-      double jw;
-      if constexpr (OP == OPK_MASS)
-        jw = it < PF ? gpf[it < PF ? it : 0] : fac[e * (NFAC * Q3) + pt];
-      else
-        jw = fac[e * (NFAC * Q3) + pt];
-      R* u = T.U(e) + lds_pt<SH, P>(pt);
-      const double f = (OP == OPK_IPR) ? src[t] : *u;
-      *u = jw * f;
-    }
-    __syncthreads();
-    ipr_chain<SH, P>(T, ne, 1);
-    store_modes<SH, P>(T, reinterpret_cast<R*>(a.out), e0, ne, 1);
-    return;
   }
 
   if (OP == OPK_DERIV) {
@@ -999,6 +1063,22 @@ __device__ Tile_<SH, P, R> make_tile_h(void* smem, const R* gtab) {
   return T;
 }
 
+// the tile of operator OP: the values tile's two buffers, or four point buffers
+template <int SH, int P, int OP, typename R>
+__device__ Tile_<SH, P, R> make_tile_op(void* smem, const R* gtab) {
+  Tile_<SH, P, R> T = make_tile_h<SH, P, R>(smem, gtab);
+  if constexpr (values_op(OP)) {
+    T.per = values_per<SH, P>();
+    T.bs = values_bs<SH, P>();
+  }
+  return T;
+}
+
+template <int SH, int P>
+constexpr size_t lds_bytes_values(int E) {
+  return sizeof(double) * (size_t)(head_h<SH, P, double>() + E * values_per<SH, P>());
+}
+
 template <int SH, int P, typename R>
 constexpr size_t lds_bytes_h(int E) {
   return sizeof(R) * (size_t)(head_h<SH, P, R>() + E * Dims<SH, P>::PER_ELEM);
@@ -1019,7 +1099,7 @@ __global__ void __launch_bounds__(512) k_block(OpArgs a) {
   const long long rem = a.n_elem - e0;
   const int ne = rem < a.E ? (int)rem : a.E;
   if (ne <= 0) return;
-  const Tile_<SH, P> T = make_tile_h<SH, P, double>(smem, a.tab);
+  const Tile_<SH, P> T = make_tile_op<SH, P, OP, double>(smem, a.tab);
   tile_body<SH, P, OP>(a, e0, ne, T);
 }
 
@@ -1052,10 +1132,10 @@ __global__ void __launch_bounds__(512) k_mixed(const BlockStatic* __restrict__ b
   a.E = b.E;
   a.pad_ = 0;
   switch (b.shape) {
-    case HEX: tile_body<HEX, P, OP>(a, tl.e0, tl.ne, make_tile_h<HEX, P, double>(smem, a.tab)); break;
-    case PRISM: tile_body<PRISM, P, OP>(a, tl.e0, tl.ne, make_tile_h<PRISM, P, double>(smem, a.tab)); break;
-    case PYR: tile_body<PYR, P, OP>(a, tl.e0, tl.ne, make_tile_h<PYR, P, double>(smem, a.tab)); break;
-    default: tile_body<TET, P, OP>(a, tl.e0, tl.ne, make_tile_h<TET, P, double>(smem, a.tab)); break;
+    case HEX: tile_body<HEX, P, OP>(a, tl.e0, tl.ne, make_tile_op<HEX, P, OP, double>(smem, a.tab)); break;
+    case PRISM: tile_body<PRISM, P, OP>(a, tl.e0, tl.ne, make_tile_op<PRISM, P, OP, double>(smem, a.tab)); break;
+    case PYR: tile_body<PYR, P, OP>(a, tl.e0, tl.ne, make_tile_op<PYR, P, OP, double>(smem, a.tab)); break;
+    default: tile_body<TET, P, OP>(a, tl.e0, tl.ne, make_tile_op<TET, P, OP, double>(smem, a.tab)); break;
   }
 }
 
