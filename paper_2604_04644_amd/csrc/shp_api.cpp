@@ -101,6 +101,8 @@ struct shp_plan_s {
   long long max_tiles = 0;  // tile slots reserved per operator
   Tiling mixed[OPK_COUNT];
   int mixed_ntiles[OPK_COUNT] = {};
+  Tiling mixed_now[OPK_COUNT];        // launch shape and LDS that go with the tile list (build_tiles)
+  size_t mixed_lds[OPK_COUNT] = {};
   bool mixed_dirty[OPK_COUNT] = {};
   bool uniform_P = true;
   int auto_mixed[7] = {2, 2, 2, 2, 2, 2, 2};
@@ -854,7 +856,16 @@ constexpr double LPT_WEIGHT[4][10] = {
     {1.23, 1.11, 1.06, 1.07, 1.07, 1.14, 1.15, 1.58, 1.44, 1.75}};
 
 static int build_tiles(shp_plan p, int opk, hipStream_t s) {
-  const int E = mixed_tiling(p, opk).E;
+  const Tiling mt = mixed_tiling(p, opk);
+  const int E = mt.E;
+  size_t lds = 0;
+  for (const auto& B : p->blocks) {
+    const bool f32 = opk == OPK_HELM_F32 || opk == OPK_LAP_F32, iso = opk == OPK_HELM_ISO || opk == OPK_LAP_ISO;
+    lds = std::max(lds, is_2d(B.d.shape) ? lds_bytes_2d(B.d.shape, B.d.P, E, opk, mt.NT)
+                        : f32            ? lds_bytes_f32(B.d.shape, B.d.P, E)
+                        : iso            ? op_lds_bytes(B.d.shape, B.d.P, OPK_HELM, E, 2)
+                                         : op_lds_bytes(B.d.shape, B.d.P, opk, E, opk == OPK_ADR ? 2 : mt.persist));
+  }
   struct T2 {
     Tile t;
     double cost;
@@ -884,6 +895,8 @@ static int build_tiles(shp_plan p, int opk, hipStream_t s) {
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return dev_fail(e, "tile list upload");
   p->mixed_ntiles[opk] = (int)host.size();
+  p->mixed_now[opk] = mt;
+  p->mixed_lds[opk] = lds;
   p->mixed_dirty[opk] = false;
   return SHP_OK;
 }
@@ -967,6 +980,13 @@ static int resolve_auto(shp_plan p, int blk, int op, hipStream_t s, int* strateg
 static bool mf_runs(int opk, int P, const Tiling& t) {
   int E, NT;
   return mf_action(opk) && t.persist == 2 && mf_helm_shape(P, &E, &NT) && t.E == E && t.NT == NT;
+}
+
+// whether the whole-mesh launch of operator opk is the matrix-core one
+static bool mf_mesh_runs(shp_plan p, int opk) {
+  int E, NT;
+  if (!mf_action(opk) || !mf_mesh(p) || !mf_helm_shape(p->blocks[0].d.P, &E, &NT)) return false;
+  return mf_runs(opk, p->blocks[0].d.P, mixed_tiling(p, opk));
 }
 
 static MfBlock mf_block(shp_plan p, int blk, const double* in, double* out) {
@@ -1093,9 +1113,8 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
     } else {
       if (p->mixed_dirty[opk])
         if (int r = build_tiles(p, opk, s)) return r;
-      const Tiling mt = mixed_tiling(p, opk);
-      size_t lds = 0;
-      for (const auto& B : p->blocks) lds = std::max(lds, lds_bytes_2d(B.d.shape, B.d.P, mt.E, opk, mt.NT));
+      const Tiling mt = p->mixed_now[opk];
+      const size_t lds = p->mixed_lds[opk];
       const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
       e = launch_mixed2d(p->blocks[0].d.P, opk, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), tiles,
                          p->mixed_ntiles[opk], in, out, p->total_phys, p->total_phys, lambda, mt.NT, lds, mt.E, s);
@@ -1129,9 +1148,8 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
       } else {
         if (p->mixed_dirty[iopk])
           if (int r = build_tiles(p, iopk, s)) return r;
-        const Tiling t = mixed_tiling(p, iopk);
-        size_t lds = 0;
-        for (const auto& B : p->blocks) lds = std::max(lds, op_lds_bytes(B.d.shape, B.d.P, OPK_HELM, t.E, 2));
+        const Tiling t = p->mixed_now[iopk];
+        const size_t lds = p->mixed_lds[iopk];
         const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)iopk * p->max_tiles;
         e = launch_iso(p->blocks[0].d.P, iopk, bst, tiles, p->mixed_ntiles[iopk], in, out, lambda, t.NT, lds, t.E, -1,
                        p->mixed_ntiles[iopk], s);
@@ -1237,17 +1255,16 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
     }
     return SHP_OK;
   }
-  const Tiling mt = mixed_tiling(p, opk);
-  const int E = mt.E, NT = mt.NT;
-  if (mf_mesh(p) && mf_runs(opk, p->blocks[0].d.P, mt)) {
+  if (mf_mesh_runs(p, opk)) {
     const hipError_t e = apply_mf(p, -1, opk, in, out, nullptr, lambda, s);
     if (e != hipSuccess) return dev_fail(e, "mixed launch");
     return SHP_OK;
   }
   if (p->mixed_dirty[opk])
     if (int r = build_tiles(p, opk, s)) return r;
-  size_t lds = 0;
-  for (const auto& B : p->blocks) lds = std::max(lds, op_lds_bytes(B.d.shape, B.d.P, opk, E, mt.persist));
+  const Tiling mt = p->mixed_now[opk];
+  const int E = mt.E, NT = mt.NT;
+  const size_t lds = p->mixed_lds[opk];
   const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
   hipError_t e = launch_mixed(p->blocks[0].d.P, opk, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), tiles,
                               p->mixed_ntiles[opk], in, out, p->total_phys, p->total_phys, lambda, NT, lds, E, mt.persist, s);
@@ -1380,9 +1397,8 @@ int shp_apply_prec(shp_plan p, int blk, int op, int strategy, int prec, const vo
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (p->mixed_dirty[tk])
     if (int r = build_tiles(p, tk, s)) return r;
-  const Tiling mt = mixed_tiling(p, tk);
-  size_t lds = 0;
-  for (const auto& B : p->blocks) lds = std::max(lds, lds_bytes_f32(B.d.shape, B.d.P, mt.E));
+  const Tiling mt = p->mixed_now[tk];
+  const size_t lds = p->mixed_lds[tk];
   if (points_per_thread((long long)mt.E * (p->blocks[0].d.Q) * p->blocks[0].d.Q * p->blocks[0].d.Q, mt.NT) == 0)
     return fail(SHP_ERR_UNSUPPORTED, "launch shape too large for the FP32 kernel's register slots");
   const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)tk * p->max_tiles;
@@ -1424,19 +1440,18 @@ int shp_apply_adr(shp_plan p, const double* adv, const double* in, double* out, 
       return fail(SHP_ERR_UNSUPPORTED, "the advection-diffusion-reaction action needs 3D blocks with precomputed factors");
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const Tiling mt = mixed_tiling(p, OPK_ADR);
-  if (mf_mesh(p) && mf_runs(OPK_ADR, p->blocks[0].d.P, mt)) {
+  if (mf_mesh_runs(p, OPK_ADR)) {
     const hipError_t e = apply_mf(p, -1, OPK_ADR, in, out, adv, lambda, s);
     if (e != hipSuccess) return dev_fail(e, "advection-diffusion-reaction launch");
     return SHP_OK;
   }
   if (p->mixed_dirty[OPK_ADR])
     if (int r = build_tiles(p, OPK_ADR, s)) return r;
+  const Tiling mt = p->mixed_now[OPK_ADR];
   const int Q = p->blocks[0].d.Q;
   if (points_per_thread((long long)mt.E * Q * Q * Q, mt.NT) == 0)
     return fail(SHP_ERR_UNSUPPORTED, "launch shape too large for the advection-diffusion-reaction kernel");
-  size_t lds = 0;
-  for (const auto& B : p->blocks) lds = std::max(lds, op_lds_bytes(B.d.shape, B.d.P, OPK_ADR, mt.E, 2));
+  const size_t lds = p->mixed_lds[OPK_ADR];
   const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)OPK_ADR * p->max_tiles;
   const hipError_t e = launch_adr(p->blocks[0].d.P, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), tiles,
                                   p->mixed_ntiles[OPK_ADR], in, out, adv, lambda, mt.NT, lds, mt.E, s);
@@ -1897,7 +1912,7 @@ int shp_tune_cache_load(shp_plan p, const char* path, int* n_applied) {
       std::string sig;
       if (!json_str(l, "blocks", &sig) || sig != mixed_signature(p)) continue;
       p->mixed[opk] = Tiling{(int)E, (int)NT, (int)V};
-      p->mixed_dirty[opk] = true;
+      drop_tiles(p, opk);
       p->auto_mixed[op] = (int)st;
       p->auto_mixed_src[op] = 1;
       ++applied;

@@ -179,6 +179,12 @@ def _stream(torch):
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+def _raw_stream(torch):
+    """_stream as an integer (for entry points with declared argument types).  Read
+    without building a Stream object, which took a fifth of a small action's time."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def c0_tet_map(verts, P: int):
     """Host call of shp_c0_tet_map: (l2g, row_ptr, col, n_global) as int64
     numpy arrays for the tetrahedra with vertex ids verts [n_elem][4]."""
@@ -209,6 +215,7 @@ class Plan:
         if not torch.cuda.is_available():
             raise RuntimeError("libshp needs a HIP device; none is visible")
         self.blocks = [(b[0], int(b[1]), int(b[2]), b[3] if len(b) > 3 else "curved") for b in blocks]
+        self._size_of = {}
         self.points = [b[4] if len(b) > 4 else "gj" for b in blocks]
         arr = (_BlockDesc * len(self.blocks))()
         for i, (sh, P, ne, geom) in enumerate(self.blocks):
@@ -305,22 +312,33 @@ class Plan:
             return {"iprod": npnt, "physderiv": npnt, "iprod_deriv": self.dim * npnt}.get(op, nc)
         return {"iprod": ne * nq, "physderiv": ne * nq, "iprod_deriv": self.dim * ne * nq}.get(op, ne * nm)
 
+    def _sizes(self, blk: int, op: str):
+        """(input values, output shape, output values) of op on block blk: fixed by
+        the plan's blocks, so worked out once."""
+        s = self._size_of.get((blk, op))
+        if s is None:
+            shape = self._out_shape(blk, op)
+            s = self._size_of[(blk, op)] = (self._in_numel(blk, op), shape, int(self._torch.Size(shape).numel()))
+        return s
+
     def apply(self, blk: int, op: str, x, out=None, lam: float = 1.0, strategy: str = "auto"):
         """y = op(x) for block blk (or the whole mesh, blk = -1); strategy
         "auto" runs the tuned or set choice, else the cost model's (when one is
         loaded), else the collocated sum-factorisation."""
         t = self._torch
-        if x.dtype != t.float64 or not x.is_cuda or not x.is_contiguous():
+        f64 = t.float64
+        if x.dtype != f64 or not x.is_cuda or not x.is_contiguous():
             raise ValueError("x must be a contiguous float64 device tensor")
-        if x.numel() != self._in_numel(blk, op):
-            raise ValueError(f"x has {x.numel()} values, {op} on block {blk} takes {self._in_numel(blk, op)}")
+        n_in, shape, n_out = self._sizes(blk, op)
+        if x.numel() != n_in:
+            raise ValueError(f"x has {x.numel()} values, {op} on block {blk} takes {n_in}")
         if out is None:
-            out = t.empty(self._out_shape(blk, op), dtype=t.float64, device=x.device)
-        elif out.dtype != t.float64 or not out.is_cuda or not out.is_contiguous() or out.numel() != int(
-                t.Size(self._out_shape(blk, op)).numel()):
+            out = t.empty(shape, dtype=f64, device=x.device)
+        elif out.dtype != f64 or not out.is_cuda or not out.is_contiguous() or out.numel() != n_out:
             raise ValueError("bad output tensor")
-        _check(lib().shp_apply(self._h, blk, OPS[op], STRATEGY[strategy], ctypes.c_void_p(x.data_ptr()),
-                               ctypes.c_void_p(out.data_ptr()), float(lam), _stream(t)))
+        code = _lib.shp_apply(self._h, blk, OPS[op], STRATEGY[strategy], x.data_ptr(), out.data_ptr(), float(lam), _raw_stream(t))
+        if code:
+            _check(code)
         return out
 
     def apply_prec(self, op: str, x, out=None, lam: float = 1.0, prec: str = "fp32", blk: int = -1,
@@ -340,15 +358,17 @@ class Plan:
             strategy = "localmat" if prec.startswith("bf16") else "sumfac_coll"
         if x.dtype != dt or not x.is_cuda or not x.is_contiguous():
             raise ValueError(f"x must be a contiguous {dt} device tensor")
-        if x.numel() != self._in_numel(blk, op):
-            raise ValueError(f"x has {x.numel()} values, {op} on block {blk} takes {self._in_numel(blk, op)}")
+        n_in, shape, _ = self._sizes(blk, op)
+        if x.numel() != n_in:
+            raise ValueError(f"x has {x.numel()} values, {op} on block {blk} takes {n_in}")
         if out is None:
-            out = t.empty(self._out_shape(blk, op), dtype=dt, device=x.device)
+            out = t.empty(shape, dtype=dt, device=x.device)
         elif out.dtype != dt or not out.is_cuda or not out.is_contiguous() or out.numel() != x.numel():
             raise ValueError("bad output tensor")
-        _check(lib().shp_apply_prec(self._h, int(blk), OPS[op], STRATEGY[strategy], PREC[prec],
-                                    ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()), float(lam),
-                                    _stream(t)))
+        code = _lib.shp_apply_prec(self._h, int(blk), OPS[op], STRATEGY[strategy], PREC[prec], x.data_ptr(),
+                                   out.data_ptr(), float(lam), _raw_stream(t))
+        if code:
+            _check(code)
         return out
 
     def set_fp32_factors(self, enable: bool = True):
@@ -381,7 +401,7 @@ class Plan:
     def apply_adr(self, x, adv, out=None, lam: float = 1.0):
         """Whole-mesh advection-diffusion-reaction action (FP64)."""
         t = self._torch
-        nc, npnt = self.totals()
+        nc, npnt = self._sizes(-1, "helmholtz")[0], self._sizes(-1, "iprod")[0]
         if x.dtype != t.float64 or not x.is_cuda or not x.is_contiguous() or x.numel() != nc:
             raise ValueError(f"x must be a contiguous float64 device tensor of {nc} values")
         if adv.dtype != t.float64 or not adv.is_cuda or not adv.is_contiguous() or adv.numel() != 3 * npnt:
@@ -390,8 +410,9 @@ class Plan:
             out = t.empty_like(x)
         elif out.dtype != t.float64 or not out.is_cuda or not out.is_contiguous() or out.numel() != nc:
             raise ValueError("bad output tensor")
-        _check(lib().shp_apply_adr(self._h, ctypes.c_void_p(adv.data_ptr()), ctypes.c_void_p(x.data_ptr()),
-                                   ctypes.c_void_p(out.data_ptr()), float(lam), _stream(t)))
+        code = _lib.shp_apply_adr(self._h, adv.data_ptr(), x.data_ptr(), out.data_ptr(), float(lam), _raw_stream(t))
+        if code:
+            _check(code)
         return out
 
     def _solve_ws(self, device):
