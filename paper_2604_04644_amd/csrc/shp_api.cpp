@@ -834,7 +834,7 @@ static Tiling mixed_tiling(shp_plan p, int opk) {
   t = Tiling{64, 512, 2};
   for (const auto& B : p->blocks) {
     // the thread-per-line tile's shape (that of the FP32 actions)
-    const int dk = helm_action(opk) ? (int)OPK_HELM_F32 : opk;
+    const int dk = helm_action(opk) && !dim2 ? (int)OPK_HELM_F32 : opk;
     Tiling d = default_tiling(B.d.shape, B.d.P, dk);
     const long long Q3 = (long long)B.d.Q * B.d.Q * B.d.Q;
     if (helm_action(opk) && !dim2 && d.E * Q3 <= 2LL * d.NT) d = default_tiling(B.d.shape, B.d.P, dk, 64 * 1024);
