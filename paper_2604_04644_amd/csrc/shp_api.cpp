@@ -228,7 +228,6 @@ Tiling default_tiling(int sh, int P, int opk, size_t lds_budget = 40 * 1024) {
     t.persist = 0;
     return t;
   }
-  if (int E, NT; mf_action(opk) && mf_helm_shape(P, &E, &NT)) return Tiling{E, NT, 2};
   if (helm && P >= 7) {
     t.E = HI_E[sh][P - 7];
     t.NT = HI_NT[sh][P - 7];
@@ -242,17 +241,11 @@ Tiling default_tiling(int sh, int P, int opk, size_t lds_budget = 40 * 1024) {
   return t;
 }
 
-// Iso-parametric launches keep 9 FP64 derivatives per owned point in
-// registers while they rebuild the geometry, so they own at most 2 points per
-// thread (4 from P = 9, where one element has more than 1024 points): as many
-// elements as fill 512 points on 256 threads, else one element on 512.
-Tiling iso_tiling(int P) {
-  const int Q3 = (P + 2) * (P + 2) * (P + 2);
-  Tiling t;
-  t.E = std::max(1, std::min(16, 512 / Q3));
-  t.NT = (t.E * Q3 <= 512) ? 256 : 512;
-  t.persist = 2;
-  return t;
+Tiling iso_tiling(int P) { return Tiling{iso_shape(P).E, iso_shape(P).NT, 2}; }
+size_t iso_lds(int sh, int P) {
+  const size_t lds = op_lds_bytes(sh, P, OPK_HELM, iso_shape(P).E, 2);
+  // a joint element has three point buffers for each coordinate besides
+  return iso_shape(P).joint ? lds + sizeof(double) * 9 * (P + 2) * (P + 2) * qpad(P + 2) : lds;
 }
 
 // A launch of n_elem elements with fewer tiles than the chip has CUs takes smaller
@@ -394,7 +387,9 @@ int shp_plan_create(shp_plan* out, const shp_block_desc* blk, int nblk) {
     B.NQ = B.d.Q * B.d.Q * B.d.Q;
     build_tables(B.d.shape, B.d.P, B.d.pts, B.tab, B.itab);
     build_mf_image(B.d.shape, B.d.P, B.tab, B.itab, B.mf);
-    build_diag_tables(B.d.shape, B.d.P, B.d.pts, B.dtab, B.ditab, B.dn);
+    build_diag_tables(B.d.shape, B.d.P, B.d.pts, B.dtab, B.ditab, B.dn.n1, B.dn.n12);
+    for (int i = 0; i < B.dn.n12; ++i) B.dn.n2 = std::max(B.dn.n2, (B.ditab[i] >> 16) + 1);
+    B.dn.n3 = (int)B.dtab.size() / (3 * B.d.Q) - B.dn.n1 - B.dn.n2;
     if (B.iso()) build_ref_weights(B.d.shape, B.d.P, B.d.pts, B.wref);
     if (B.d.P <= LOCALMAT_MAX_P && !B.iso()) {
       int q3p, kp;
@@ -608,8 +603,7 @@ int shp_plan_set_geometry(shp_plan p, int blk, const double* jac, void* stream) 
     if (e != hipSuccess) return dev_fail(e, "coordinate copy");
     const Tiling t = iso_tiling(B.d.P);
     e = launch_iso_check(B.d.P, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), blk, t.E,
-                         (B.d.n_elem + t.E - 1) / t.E, t.NT, op_lds_bytes(B.d.shape, B.d.P, OPK_HELM, t.E, 2),
-                         status, s);
+                         (B.d.n_elem + t.E - 1) / t.E, t.NT, iso_lds(B.d.shape, B.d.P), status, s);
     if (e != hipSuccess) return dev_fail(e, "iso-parametric geometry check launch");
   } else {
   GeomArgs g;
@@ -815,34 +809,34 @@ static bool mf_mesh(shp_plan p) {
   return p->uniform_P && !is_2d(p->blocks[0].d.shape) && (int)p->blocks.size() <= MF_MAX_BLK;
 }
 
-// Build and upload the whole-mesh tile list of one operator: tiles of E
-// elements from every block, heaviest first (longest-processing-time order).
-static Tiling mixed_tiling(shp_plan p, int opk) {
-  // the FP32 actions follow the FP64 action's launch shape when one is set
-  Tiling t = p->mixed[opk == OPK_HELM_F32 ? (int)OPK_HELM : opk == OPK_LAP_F32 ? (int)OPK_LAP : opk];
-  if (t.E > 0 && t.NT > 0) return t;
+// the default launch shape of the whole-mesh launch of operator opk
+static Tiling default_mixed(shp_plan p, int opk) {
   if (opk == OPK_HELM_ISO || opk == OPK_LAP_ISO) return iso_tiling(p->blocks[0].d.P);
   const int P0 = p->blocks[0].d.P;
   const bool dim2 = is_2d(p->blocks[0].d.shape);
-  if (int E, NT; mf_action(opk) && mf_mesh(p) && mf_helm_shape(P0, &E, &NT)) return Tiling{E, NT, 2};
   if (helm_action(opk) && p->uniform_P && P0 >= 7 && !dim2) {
+    Tiling t;
     t.E = HI_MESH_E[P0 - 7];
     t.NT = HI_MESH_NT[P0 - 7];
     t.persist = 2;
     return t;
   }
-  t = Tiling{64, 512, 2};
+  Tiling t{64, 512, 2};
   for (const auto& B : p->blocks) {
-    // the thread-per-line tile's shape (that of the FP32 actions)
-    const int dk = helm_action(opk) && !dim2 ? (int)OPK_HELM_F32 : opk;
-    Tiling d = default_tiling(B.d.shape, B.d.P, dk);
+    Tiling d = default_tiling(B.d.shape, B.d.P, opk);
     const long long Q3 = (long long)B.d.Q * B.d.Q * B.d.Q;
-    if (helm_action(opk) && !dim2 && d.E * Q3 <= 2LL * d.NT) d = default_tiling(B.d.shape, B.d.P, dk, 64 * 1024);
+    if (helm_action(opk) && !dim2 && d.E * Q3 <= 2LL * d.NT) d = default_tiling(B.d.shape, B.d.P, opk, 64 * 1024);
     t.E = std::min(t.E, d.E);
     t.NT = std::min(t.NT, d.NT);
     t.persist = std::min(t.persist, d.persist);
   }
   return dim2 ? t : spread(t, p->total_elem, opk);
+}
+
+static Tiling mixed_tiling(shp_plan p, int opk) {
+  // the FP32 actions follow the FP64 action's launch shape when one is set
+  const Tiling t = p->mixed[opk == OPK_HELM_F32 ? (int)OPK_HELM : opk == OPK_LAP_F32 ? (int)OPK_LAP : opk];
+  return t.E > 0 && t.NT > 0 ? t : default_mixed(p, opk);
 }
 
 // Relative cost of one element by shape (hex, prism, pyramid, tet) and
@@ -855,6 +849,8 @@ constexpr double LPT_WEIGHT[4][10] = {
     {1.03, 1.08, 1.04, 0.99, 1.03, 1.03, 1.08, 1.05, 1.28, 1.65},
     {1.23, 1.11, 1.06, 1.07, 1.07, 1.14, 1.15, 1.58, 1.44, 1.75}};
 
+// Build and upload the whole-mesh tile list of one operator: tiles of E
+// elements from every block, heaviest first (longest-processing-time order).
 static int build_tiles(shp_plan p, int opk, hipStream_t s) {
   const Tiling mt = mixed_tiling(p, opk);
   const int E = mt.E;
@@ -863,7 +859,7 @@ static int build_tiles(shp_plan p, int opk, hipStream_t s) {
     const bool f32 = opk == OPK_HELM_F32 || opk == OPK_LAP_F32, iso = opk == OPK_HELM_ISO || opk == OPK_LAP_ISO;
     lds = std::max(lds, is_2d(B.d.shape) ? lds_bytes_2d(B.d.shape, B.d.P, E, opk, mt.NT)
                         : f32            ? lds_bytes_f32(B.d.shape, B.d.P, E)
-                        : iso            ? op_lds_bytes(B.d.shape, B.d.P, OPK_HELM, E, 2)
+                        : iso            ? iso_lds(B.d.shape, B.d.P)
                                          : op_lds_bytes(B.d.shape, B.d.P, opk, E, opk == OPK_ADR ? 2 : mt.persist));
   }
   struct T2 {
@@ -976,17 +972,26 @@ static int resolve_auto(shp_plan p, int blk, int op, hipStream_t s, int* strateg
   return SHP_OK;
 }
 
-// whether launch shape t of operator opk is the matrix-core launch's
-static bool mf_runs(int opk, int P, const Tiling& t) {
-  int E, NT;
-  return mf_action(opk) && t.persist == 2 && mf_helm_shape(P, &E, &NT) && t.E == E && t.NT == NT;
+static bool unset_or(const Tiling& set, const Tiling& t) {
+  return set.E <= 0 || set.NT <= 0 || (set.E == t.E && set.NT == t.NT && set.persist == t.persist);
 }
 
-// whether the whole-mesh launch of operator opk is the matrix-core one
+// Whether the matrix-core launch takes operator opk: at the orders that have one it
+// stands in for the thread-per-line tile of the default launch shape (same bits, see
+// its header), and runs under its own shape; any other shape set by the caller or the
+// tuner runs as set.
+static bool mf_block_runs(const Block& B, int opk) {
+  int E, NT;
+  if (!mf_action(opk) || is_2d(B.d.shape) || !mf_helm_shape(B.d.P, &E, &NT)) return false;
+  const Tiling& set = B.tiling[opk];
+  return unset_or(set, Tiling{E, NT, 2}) || unset_or(set, default_tiling(B.d.shape, B.d.P, opk));
+}
+
 static bool mf_mesh_runs(shp_plan p, int opk) {
   int E, NT;
   if (!mf_action(opk) || !mf_mesh(p) || !mf_helm_shape(p->blocks[0].d.P, &E, &NT)) return false;
-  return mf_runs(opk, p->blocks[0].d.P, mixed_tiling(p, opk));
+  const Tiling& set = p->mixed[opk];
+  return unset_or(set, Tiling{E, NT, 2}) || unset_or(set, default_mixed(p, opk));
 }
 
 static MfBlock mf_block(shp_plan p, int blk, const double* in, double* out) {
@@ -1029,8 +1034,8 @@ static hipError_t apply_mf(shp_plan p, int blk, int opk, const double* in, doubl
 static hipError_t apply_block(shp_plan p, int blk, int opk, const double* in, double* out, long long cs,
                               double lambda, hipStream_t s) {
   const Block& B = p->blocks[blk];
+  if (mf_block_runs(B, opk)) return apply_mf(p, blk, opk, in, out, nullptr, lambda, s);
   const Tiling t = effective(B.tiling[opk], B.d.shape, B.d.P, opk, B.d.n_elem);
-  if (mf_runs(opk, B.d.P, t)) return apply_mf(p, blk, opk, in, out, nullptr, lambda, s);
   OpArgs a{};
   a.tab = reinterpret_cast<const double*>(p->ws + B.off_tab);
   a.itab = reinterpret_cast<const int*>(p->ws + B.off_itab);
@@ -1144,7 +1149,7 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
         const Block& B = p->blocks[blk];
         const Tiling t = iso_tiling(B.d.P);
         e = launch_iso(B.d.P, iopk, bst, nullptr, 0, in, out, lambda, t.NT,
-                       op_lds_bytes(B.d.shape, B.d.P, OPK_HELM, t.E, 2), t.E, blk, (B.d.n_elem + t.E - 1) / t.E, s);
+                       iso_lds(B.d.shape, B.d.P), t.E, blk, (B.d.n_elem + t.E - 1) / t.E, s);
       } else {
         if (p->mixed_dirty[iopk])
           if (int r = build_tiles(p, iopk, s)) return r;

@@ -53,7 +53,7 @@ void build_dense_deriv(int sh, int P, int pts, std::vector<double>& dm, int& Q3p
 struct DiagDims {
   int n1 = 0, n2 = 0, n3 = 0, n12 = 0;
 };
-void build_diag_tables(int sh, int P, int pts, std::vector<double>& dt, std::vector<int>& di, DiagDims& n);
+void build_diag_tables(int sh, int P, int pts, std::vector<double>& dt, std::vector<int>& di, int& n1, int& n12);
 // diag(lambda M + L) of the elements of up to DIAG_MAX_BLK blocks with the same Q,
 // from their factors fac [n_elem][NFAC][Q^3]; diag [n_elem][NP] per block
 constexpr int DIAG_MAX_BLK = 8;

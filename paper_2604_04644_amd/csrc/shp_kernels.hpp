@@ -589,10 +589,10 @@ __device__ void grad3T(const Tile_<SH, P, R>& T, int ne) {
 // separate stages; they decompose each task index once and keep several lines
 // of LDS reads in flight.
 
-// bwd_p (G2 -> U) and, from the U line still in registers, the eta1
+// bwd_p (buffer gbuf -> U) and, from the U line still in registers, the eta1
 // derivative G0 = D_0 U: one task per (e, j, k)
 template <int SH, int P, typename R>
-__device__ void bwd_p_grad0(const Tile_<SH, P, R>& T, int ne) {
+__device__ void bwd_p_grad0(const Tile_<SH, P, R>& T, int ne, int gbuf = 2) {
   using D = Dims<SH, P>;
   constexpr int Q = D::Q, n = D::n, QP = D::QP;
   for (int t = tid(); t < ne * Q * Q; t += nthr()) {
@@ -601,7 +601,7 @@ __device__ void bwd_p_grad0(const Tile_<SH, P, R>& T, int ne) {
     const int rem = t - e * (Q * Q);
     const int j = rem / Q, k = rem - j * Q;
     const int o = j * QP + k;
-    const R* G = T.G(e, 2) + o;
+    const R* G = T.G(e, gbuf) + o;
     R g[n];
 #pragma unroll
     for (int p = 0; p < n; ++p) g[p] = G[p * Q * QP];

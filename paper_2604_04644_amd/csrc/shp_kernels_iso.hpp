@@ -16,6 +16,42 @@
 
 namespace shp {
 
+// cofactors of d x_c/d eta_d (A, at c*3 + d): d eta_d/d x_i = C[d*3 + i] / det; returns det
+__device__ __forceinline__ double iso_cofactors(const double* A, double* C) {
+  C[0] = A[4] * A[8] - A[5] * A[7];
+  C[1] = A[2] * A[7] - A[1] * A[8];
+  C[2] = A[1] * A[5] - A[2] * A[4];
+  C[3] = A[5] * A[6] - A[3] * A[8];
+  C[4] = A[0] * A[8] - A[2] * A[6];
+  C[5] = A[2] * A[3] - A[0] * A[5];
+  C[6] = A[3] * A[7] - A[4] * A[6];
+  C[7] = A[1] * A[6] - A[0] * A[7];
+  C[8] = A[0] * A[4] - A[1] * A[3];
+  return A[0] * C[0] + A[1] * C[3] + A[2] * C[6];
+}
+
+// d x_c/d eta_d and the reference weight of one point -> its 7 factors f; false when
+// the determinant is not positive or a factor not finite.
+__device__ __forceinline__ bool iso_factors(const double* A, double w, double* f) {
+  double M[9];  // d eta_d / d x_i at d*3 + i
+  const double det = iso_cofactors(A, M);
+  const double id = 1.0 / det;
+#pragma unroll
+  for (int c = 0; c < 9; ++c) M[c] *= id;
+  const double jw = w * det;
+  f[0] = jw;
+  f[1] = jw * (M[0] * M[0] + M[1] * M[1] + M[2] * M[2]);
+  f[2] = jw * (M[0] * M[3] + M[1] * M[4] + M[2] * M[5]);
+  f[3] = jw * (M[0] * M[6] + M[1] * M[7] + M[2] * M[8]);
+  f[4] = jw * (M[3] * M[3] + M[4] * M[4] + M[5] * M[5]);
+  f[5] = jw * (M[3] * M[6] + M[4] * M[7] + M[5] * M[8]);
+  f[6] = jw * (M[6] * M[6] + M[7] * M[7] + M[8] * M[8]);
+  bool good = det > 0.0 && isfinite(det);
+#pragma unroll
+  for (int c = 1; c < NFAC; ++c) good = good && isfinite(f[c]);
+  return good;
+}
+
 // d x/d eta at the tile's points -> the 7 factors of each point a thread owns
 // (slots as in the geometry prefetch); returns false when a determinant is not
 // positive or a factor not finite.  Ends with a barrier (LDS free again).
@@ -60,34 +96,7 @@ __device__ __forceinline__ bool iso_geometry(const double* __restrict__ xco, con
     if (t < ne * Q3) {
       const int pt = t - (t / Q3) * Q3;
       const double* A = J[it];
-      // cofactors: inverse[d][i] = d eta_d / d x_i = cof[i][d] / det
-      const double c00 = A[4] * A[8] - A[5] * A[7];
-      const double c01 = A[5] * A[6] - A[3] * A[8];
-      const double c02 = A[3] * A[7] - A[4] * A[6];
-      const double det = A[0] * c00 + A[1] * c01 + A[2] * c02;
-      const double id = 1.0 / det;
-      double M[9];  // d eta_d / d x_i at d*3 + i
-      M[0] = c00 * id;
-      M[1] = (A[2] * A[7] - A[1] * A[8]) * id;
-      M[2] = (A[1] * A[5] - A[2] * A[4]) * id;
-      M[3] = c01 * id;
-      M[4] = (A[0] * A[8] - A[2] * A[6]) * id;
-      M[5] = (A[2] * A[3] - A[0] * A[5]) * id;
-      M[6] = c02 * id;
-      M[7] = (A[1] * A[6] - A[0] * A[7]) * id;
-      M[8] = (A[0] * A[4] - A[1] * A[3]) * id;
-      const double jw = wref[pt] * det;
-      double* f = g.v[it];
-      f[0] = jw;
-      f[1] = jw * (M[0] * M[0] + M[1] * M[1] + M[2] * M[2]);
-      f[2] = jw * (M[0] * M[3] + M[1] * M[4] + M[2] * M[5]);
-      f[3] = jw * (M[0] * M[6] + M[1] * M[7] + M[2] * M[8]);
-      f[4] = jw * (M[3] * M[3] + M[4] * M[4] + M[5] * M[5]);
-      f[5] = jw * (M[3] * M[6] + M[4] * M[7] + M[5] * M[8]);
-      f[6] = jw * (M[6] * M[6] + M[7] * M[7] + M[8] * M[8]);
-      bool good = det > 0.0 && isfinite(det);
-#pragma unroll
-      for (int c = 1; c < NFAC; ++c) good = good && isfinite(f[c]);
+      const bool good = iso_factors(A, wref[pt], g.v[it]);
       ok = ok && good;
     }
   }
@@ -134,11 +143,188 @@ __device__ __forceinline__ void iso_helm(const BlockStatic& b, const Tile& tl, c
   helm_tile<SH, P, OP, PPT>(a, tl.e0, tl.ne, T, g, false, []() {});
 }
 
+// ---------------------------------------------------------------------------
+// one element per work-group, coordinates and solution through the stages together
+// ---------------------------------------------------------------------------
+// The three coordinates and the solution are the NF = 4 fields (3 for the geometry
+// check) of one element and run through the forward stages as four "elements" of the
+// tile: a stage has 4 Q^2 line tasks, one per thread, and the work-group waits on 11
+// barriers instead of 28.  A coordinate takes three point buffers, G2 in place of U.
+
+// the tile of the fields: field c at c * per
+template <int SH, int P>
+__device__ Tile_<SH, P> make_tile_iso(double* smem, const double* gtab) {
+  Tile_<SH, P> T = make_tile_h<SH, P, double>(smem, gtab);
+  T.per = 3 * T.bs;
+  return T;
+}
+
+// eta2 and eta3 collocation derivatives of the fields: G1 = D_1 U and, in place of U,
+// D_2 U; of field 3 (the solution, whose U stays) into G2
+template <int SH, int P, int NF>
+__device__ __forceinline__ void iso_grad12(const Tile_<SH, P>& T) {
+  using D = Dims<SH, P>;
+  constexpr int Q = D::Q, QP = D::QP;
+  const int t = min(tid(), NF * Q * Q - 1);
+  const int c = t / (Q * Q), r2 = t - c * (Q * Q), i = r2 / Q, b = r2 - i * Q;
+  const double *s1 = T.U(c) + i * Q * QP + b, *s2 = T.U(c) + (i * Q + b) * QP;
+  double v1[Q], v2[Q];
+#pragma unroll
+  for (int l = 0; l < Q; ++l) {
+    v1[l] = s1[l * QP];
+    v2[l] = s2[l];
+  }
+  __syncthreads();
+  if (tid() < NF * Q * Q) {
+    double* g = T.G(c, 1) + i * Q * QP + b;
+    ctab_t Dm = launder(T.ct) + D::L.D + 1 * Q * Q;
+#pragma unroll
+    for (int m = 0; m < Q; ++m) {
+      double s = 0.0;
+#pragma unroll
+      for (int l = 0; l < Q; ++l) s = fma(Dm[m * Q + l], v1[l], s);
+      g[m * QP] = s;
+    }
+    g = (c < 3 ? T.U(c) : T.G(c, 2)) + (i * Q + b) * QP;
+    Dm = launder(T.ct) + D::L.D + 2 * Q * Q;
+#pragma unroll
+    for (int m = 0; m < Q; ++m) {
+      double s = 0.0;
+#pragma unroll
+      for (int l = 0; l < Q; ++l) s = fma(Dm[m * Q + l], v2[l], s);
+      g[m] = s;
+    }
+  }
+}
+
+// coefficients -> the fields' collocated derivatives (and the solution's values);
+// leaves the threads at a barrier
+template <int SH, int P, int NF>
+__device__ __forceinline__ void iso_fields(const double* __restrict__ xco, const double* __restrict__ in,
+                                           long long e, const Tile_<SH, P>& T) {
+  constexpr int NP = Dims<SH, P>::NP, NT = iso_shape(P).NT;
+  constexpr int XS = (3 * NP + NT - 1) / NT, US = NF == 4 ? (NP + NT - 1) / NT : 0;
+  const double *xs = xco + e * (3 * NP), *us = in + e * NP;
+  double xv[XS], uv[US ? US : 1];
+  // every slot loads (past the end the last coefficient, written to its own place)
+#pragma unroll
+  for (int s = 0; s < XS; ++s) xv[s] = xs[min(tid() + s * NT, 3 * NP - 1)];
+#pragma unroll
+  for (int s = 0; s < US; ++s) uv[s] = us[min(tid() + s * NT, NP - 1)];
+#pragma unroll
+  for (int s = 0; s < XS; ++s) {
+    const int t = min(tid() + s * NT, 3 * NP - 1);
+    const int c = t / NP;
+    T.U(c)[t - c * NP] = xv[s];
+  }
+#pragma unroll
+  for (int s = 0; s < US; ++s) T.U(3)[min(tid() + s * NT, NP - 1)] = uv[s];
+  __syncthreads();
+  // modes in U -> F in G0 -> G in G1 -> U, with G0 = D_0 U from the same task
+  bwd_r<SH, P, false>(T, NF, -1, 0);
+  __syncthreads();
+  bwd_q<SH, P, false>(T, NF, 0, 1);
+  __syncthreads();
+  bwd_p_grad0<SH, P>(T, NF, 1);
+  __syncthreads();
+  iso_grad12<SH, P, NF>(T);
+  __syncthreads();
+}
+
+// d x_c/d eta_d of the point at lp -> A[c*3 + d]
+template <int SH, int P>
+__device__ __forceinline__ void iso_derivs(const Tile_<SH, P>& T, int lp, double* A) {
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    A[c * 3 + 0] = T.G(c, 0)[lp];
+    A[c * 3 + 1] = T.G(c, 1)[lp];
+    A[c * 3 + 2] = T.U(c)[lp];
+  }
+}
+
+template <int SH, int P, int OP>
+__device__ __forceinline__ void iso_joint(const BlockStatic& b, const Tile& tl, const double* in, double* out,
+                                          double lambda, double* smem) {
+  using D = Dims<SH, P>;
+  constexpr int Q3 = D::Q3, NT = iso_shape(P).NT, PPT = (Q3 + NT - 1) / NT;
+  OpArgs a;
+  a.tab = b.tab;
+  a.itab = b.itab;
+  const Tile_<SH, P> T = make_tile_iso<SH, P>(smem, b.tab);
+  load_tables_helm<SH, P>(a, T);
+  double w[PPT];
+#pragma unroll
+  for (int it = 0; it < PPT; ++it) w[it] = b.wref[min(tid() + it * NT, Q3 - 1)];
+  iso_fields<SH, P, 4>(b.xco, in, tl.e0, T);
+  Tile_<SH, P> S = T;  // the solution's buffers alone
+  S.el += 3 * T.per;
+#pragma unroll
+  for (int it = 0; it < PPT; ++it) {
+    const int pt = tid() + it * NT;
+    if (pt < Q3) {
+      const int lp = lds_pt<SH, P>(pt);
+      double A[9], C[9], r[3];
+      iso_derivs<SH, P>(T, lp, A);
+      // jw (d eta/d x)(d eta/d x)^T d u/d eta = (w / det) C C^T d u/d eta: the factors
+      // themselves are not formed
+      const double det = iso_cofactors(A, C), wd = w[it] / det;
+      double *p0 = S.G(0, 0) + lp, *p1 = S.G(0, 1) + lp, *p2 = S.G(0, 2) + lp;
+      const double d0 = *p0, d1 = *p1, d2 = *p2;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) r[i] = wd * (C[i] * d0 + C[3 + i] * d1 + C[6 + i] * d2);
+      *p0 = C[0] * r[0] + C[1] * r[1] + C[2] * r[2];
+      *p1 = C[3] * r[0] + C[4] * r[1] + C[5] * r[2];
+      *p2 = C[6] * r[0] + C[7] * r[1] + C[8] * r[2];
+      if (OP == OPK_HELM) {
+        double* u = S.U(0) + lp;
+        *u = lambda * (w[it] * det) * (*u);
+      }
+    }
+  }
+  __syncthreads();
+  grad12<SH, P, true>(S, 1);
+  __syncthreads();
+  grad0T_ipr_p<SH, P>(S, 1, OP == OPK_HELM);
+  __syncthreads();
+  ipr_q<SH, P, false>(S, 1, -1, 0);
+  __syncthreads();
+  ipr_r<SH, P, false>(S, 1, 0, 1, false);
+  __syncthreads();
+  store_modes<SH, P>(S, out, tl.e0, 1, 1);
+}
+
+template <int SH, int P>
+__device__ __forceinline__ void iso_joint_check(const BlockStatic& b, const Tile& tl, double* smem, int* status) {
+  using D = Dims<SH, P>;
+  OpArgs a;
+  a.tab = b.tab;
+  a.itab = b.itab;
+  const Tile_<SH, P> T = make_tile_iso<SH, P>(smem, b.tab);
+  load_tables_helm<SH, P>(a, T);
+  iso_fields<SH, P, 3>(b.xco, b.xco, tl.e0, T);
+  bool ok = true;
+  for (int pt = tid(); pt < D::Q3; pt += nthr()) {
+    double A[9], f[NFAC];
+    iso_derivs<SH, P>(T, lds_pt<SH, P>(pt), A);
+    ok = iso_factors(A, b.wref[pt], f) && ok;
+  }
+  if (!ok) atomicOr(status, 1);
+}
+
+template <int SH, int P, int OP, int PPT>
+__device__ __forceinline__ void iso_action(const BlockStatic& b, const Tile& tl, const double* in, double* out,
+                                           double lambda, double* smem) {
+  if constexpr (iso_shape(P).joint)
+    iso_joint<SH, P, OP>(b, tl, in, out, lambda, smem);
+  else
+    iso_helm<SH, P, OP, PPT>(b, tl, in, out, lambda, smem);
+}
+
 // Laplacian (OP = OPK_LAP) or Helmholtz (OPK_HELM) action of iso-parametric
 // blocks of order P, one tile per work-group; in/out are whole-mesh buffers,
 // or one block's buffers when blk_only >= 0.
 template <int P, int OP, int PPT>
-__global__ void __launch_bounds__(512) k_helm_mixed_iso(const BlockStatic* __restrict__ blocks,
+__global__ void __launch_bounds__(iso_shape(P).NT) k_helm_mixed_iso(const BlockStatic* __restrict__ blocks,
                                                         const Tile* __restrict__ tiles, int ntiles, const double* in,
                                                         double* out, double lambda, int blk_only, int E_only) {
   extern __shared__ double smem[];
@@ -148,15 +334,16 @@ __global__ void __launch_bounds__(512) k_helm_mixed_iso(const BlockStatic* __res
   const double* bin = in + (blk_only >= 0 ? 0 : b.coeff_off);
   double* bout = out + (blk_only >= 0 ? 0 : b.coeff_off);
   switch (b.shape) {
-    case HEX: iso_helm<HEX, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
-    case PRISM: iso_helm<PRISM, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
-    case PYR: iso_helm<PYR, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
-    default: iso_helm<TET, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
+    case HEX: iso_action<HEX, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
+    case PRISM: iso_action<PRISM, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
+    case PYR: iso_action<PYR, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
+    default: iso_action<TET, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
   }
 }
 
 template <int SH, int P, int PPT>
 __device__ __forceinline__ void iso_check_tile(const BlockStatic& b, const Tile& tl, double* smem, int* status) {
+  if constexpr (iso_shape(P).joint) return iso_joint_check<SH, P>(b, tl, smem, status);
   OpArgs a;
   a.tab = b.tab;
   a.itab = b.itab;
@@ -169,7 +356,7 @@ __device__ __forceinline__ void iso_check_tile(const BlockStatic& b, const Tile&
 // The geometry of block blk's tiles only: status set to 1 when some point has
 // a non-positive determinant or a non-finite factor.
 template <int P, int PPT>
-__global__ void __launch_bounds__(512) k_iso_check(const BlockStatic* __restrict__ blocks, int blk, int E,
+__global__ void __launch_bounds__(iso_shape(P).NT) k_iso_check(const BlockStatic* __restrict__ blocks, int blk, int E,
                                                    int* __restrict__ status) {
   extern __shared__ double smem[];
   Tile tl;

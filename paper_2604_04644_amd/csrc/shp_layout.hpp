@@ -128,4 +128,19 @@ constexpr int ICOL = 5;
 constexpr int NFAC = 7;
 constexpr int NDXI = 9;
 
+// Iso-parametric launches: elements and threads of a work-group at order P, and whether
+// the coordinates and the solution of its element run through the stages together.
+#ifndef ISO_E
+#define ISO_E {16, 8, 4, 1, 1, 1, 1, 1, 1, 1}
+#define ISO_NT {256, 256, 256, 256, 256, 256, 384, 448, 512, 512}
+#endif
+struct IsoShape {
+  int E, NT;
+  bool joint;
+};
+constexpr IsoShape iso_shape(int P) {
+  constexpr int E[10] = ISO_E;
+  constexpr int NT[10] = ISO_NT;
+  return IsoShape{E[P - 1], NT[P - 1], P >= 4 && P <= 9};
+}
 }  // namespace shp

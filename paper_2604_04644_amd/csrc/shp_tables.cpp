@@ -344,7 +344,7 @@ void build_localmat(int sh, int P, int pts, std::vector<double>& bcat, int& Q3p,
 //   doubles: T1[3][n1][Q] T2[3][n2][Q] T3[3][n3][Q]
 //   ints:    per distinct (eta1, eta2) pair, eta1 factor + 65536 x eta2 factor
 //            [n12]; per mode, pair + 65536 x eta3 factor [NP]
-void build_diag_tables(int sh, int P, int pts, std::vector<double>& dt, std::vector<int>& di, DiagDims& n) {
+void build_diag_tables(int sh, int P, int pts, std::vector<double>& dt, std::vector<int>& di, int& n1, int& n12) {
   const int Q = P + 2;
   std::vector<double> z(3 * Q), w(3 * Q);
   for (int d = 0; d < 3; ++d) rule_1d(Q, alpha_dir(sh, d), pts, z.data() + d * Q, w.data() + d * Q);
@@ -364,10 +364,8 @@ void build_diag_tables(int sh, int P, int pts, std::vector<double>& dt, std::vec
         const int i1 = find(fac[0], f[0]), i2 = find(fac[1], f[1]), i3 = find(fac[2], f[2]);
         modes.push_back(find(pairs, i1 + 65536 * i2) + 65536 * i3);
       }
-  n.n1 = (int)fac[0].size();
-  n.n2 = (int)fac[1].size();
-  n.n3 = (int)fac[2].size();
-  n.n12 = (int)pairs.size();
+  n1 = (int)fac[0].size();
+  n12 = (int)pairs.size();
   dt.clear();
   for (int d = 0; d < 3; ++d)
     for (int type = 0; type < 3; ++type)
