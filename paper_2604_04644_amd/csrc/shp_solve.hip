@@ -146,15 +146,17 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ part, 
   __syncthreads();  // sh is free again
   return s;
 }
-// the work-group's sum of acc to part[blockIdx.x]
+// the work-group's sum of acc to part[blockIdx.x]: the halvings' order, with the last
+// six in the first wave's registers (one barrier, not nine)
 __device__ __forceinline__ void store_partial(double acc, double* __restrict__ part, double* sh) {
   sh[threadIdx.x] = acc;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+  if (threadIdx.x >= 64) return;
+  const int l = threadIdx.x;
+  double s = (sh[l] + sh[l + 128]) + (sh[l + 64] + sh[l + 192]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
+  if (l == 0) part[blockIdx.x] = s;
 }
 
 // partials of r^T z, z = r / diag (rounded as in k_jacobi, not stored)
@@ -175,23 +177,32 @@ __global__ void __launch_bounds__(256) k_rz(const T* __restrict__ r, const T* __
 // r -= alpha q, and the per-block partials of the new r^T z (z = r / diag, not
 // stored).  RZ is in its slot, PQ the sum of the partials pq; it also goes to its
 // slot for the host's check.  Launched on NB blocks of 256 threads, so element i
-// goes to the same thread, in the same order, as in k_dot.
+// goes to the same thread, in the same order, as in k_dot.  A thread's first operands
+// are on their way before the partials are summed.
 template <typename T>
 __global__ void __launch_bounds__(256) k_cg1_rz(T* __restrict__ d, T* __restrict__ r, const T* __restrict__ p,
                                                 const T* __restrict__ q, const T* __restrict__ dg,
                                                 const double* __restrict__ pq, long long n, double* __restrict__ slot,
                                                 int rz, double* __restrict__ part) {
   __shared__ double sh[256];
+  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  T dv = 0, pv = 0, rv = 0, qv = 0, gv = 1;
+  auto load = [&] {
+    if (i < n) dv = d[i], pv = p[i], rv = r[i], qv = q[i], gv = dg[i];
+  };
+  load();
   const double vpq = sum_partials(pq, sh);
   if (blockIdx.x == 0 && threadIdx.x == 0) slot[PQ] = vpq;
   const T alpha = vpq > 0.0 ? (T)(slot[rz] / vpq) : (T)0;  // 0 on breakdown, caught by the host check
   double acc = 0.0;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-    d[i] += alpha * p[i];
-    const T ri = r[i] - alpha * q[i];
+  while (i < n) {
+    d[i] = dv + alpha * pv;
+    const T ri = rv - alpha * qv;
     r[i] = ri;
-    const T zi = ri / dg[i];
+    const T zi = ri / gv;
     acc = fma((double)ri, (double)zi, acc);
+    i += (long long)gridDim.x * blockDim.x;
+    load();
   }
   store_partial(acc, part, sh);
 }
@@ -210,8 +221,8 @@ __device__ __forceinline__ double step_beta(const double* __restrict__ part, dou
 }
 // the next search direction z + beta p, z = r / diag; first: z
 template <typename T>
-__device__ __forceinline__ T next_p(T r, T dg, T beta, const T* p, int first) {
-  return first ? r / dg : r / dg + beta * *p;
+__device__ __forceinline__ T next_p(T r, T dg, T beta, T p, int first) {
+  return first ? r / dg : r / dg + beta * p;
 }
 
 // p = z + beta p with z recomputed, rounded as in k_jacobi
@@ -220,9 +231,18 @@ __global__ void __launch_bounds__(256) k_cg2_r(T* __restrict__ p, const T* __res
                                                const double* __restrict__ part, double* __restrict__ slot, int rz,
                                                int first, long long n) {
   __shared__ double sh[256];
+  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  T rv = 0, gv = 1, pv = 0;
+  auto load = [&] {
+    if (i < n) rv = r[i], gv = dg[i], pv = p[i];
+  };
+  load();
   const T beta = (T)step_beta(part, slot, rz, first, sh);
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    p[i] = next_p(r[i], dg[i], beta, p + i, first);
+  while (i < n) {
+    p[i] = next_p(rv, gv, beta, pv, first);
+    i += (long long)gridDim.x * blockDim.x;
+    load();
+  }
 }
 
 __global__ void k_to_float(const double* __restrict__ a, float* __restrict__ b, long long n) {
@@ -275,17 +295,23 @@ __global__ void __launch_bounds__(256) k_c0_gather_p(const int64_t* __restrict__
                                                      double* __restrict__ slot, int rz, int first,
                                                      T* __restrict__ xl) {
   __shared__ double sh[256];
-  const T beta = (T)step_beta(part, slot, rz, first, sh);
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n_local;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int64_t g = l2g[i];
-    T v = (T)0;
+  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t g = -1;
+  T rv = 0, gv = 1, pv = 0;
+  auto load = [&] {
+    g = i < n_local ? l2g[i] : -1;
     if (g != -1) {
       const int64_t k = g >= 0 ? g : -2 - g;
-      v = next_p(r[k], dg[k], beta, p + k, first);
-      if (g < 0) v = -v;
+      rv = r[k], gv = dg[k], pv = p[k];
     }
-    xl[i] = v;
+  };
+  load();  // on its way while the partials are summed
+  const T beta = (T)step_beta(part, slot, rz, first, sh);
+  while (i < n_local) {
+    const T v = next_p(rv, gv, beta, pv, first);
+    xl[i] = g >= 0 ? v : g == -1 ? (T)0 : -v;
+    i += (long long)gridDim.x * blockDim.x;
+    load();
   }
 }
 
@@ -302,13 +328,23 @@ __global__ void __launch_bounds__(256) k_c0_scatter_dot(const int64_t* __restric
   double dot = 0.0;
   for (long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x; g < n_global;
        g += (long long)gridDim.x * blockDim.x) {
-    const T pn = next_p(r[g], dg[g], beta, p + g, first);
+    const int64_t j0 = row_ptr[g], j1 = row_ptr[g + 1];
+    const T rv = r[g], gv = dg[g], pv = p[g];
+    // four copies at a time, their loads in flight together (a DOF has one copy inside
+    // an element and up to 8 or more at a vertex), summed in ascending order
     T acc = 0;
-    const int64_t j1 = row_ptr[g + 1];
-    for (int64_t j = row_ptr[g]; j < j1; ++j) {
-      const int64_t c = col[j];
-      acc += c >= 0 ? yl[c] : -yl[-1 - c];
+    for (int64_t j = j0; j < j1; j += 4) {
+      int64_t c[4];
+      T y[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c[k] = col[j + k < j1 ? j + k : j];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) y[k] = yl[c[k] >= 0 ? c[k] : -1 - c[k]];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (j + k < j1) acc += c[k] >= 0 ? y[k] : -y[k];
     }
+    const T pn = next_p(rv, gv, beta, pv, first);
     q[g] = acc;
     p_new[g] = pn;
     dot = fma((double)pn, (double)acc, dot);
