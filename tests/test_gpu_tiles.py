@@ -1,0 +1,104 @@
+"""GPU parity at the edges of tiles and launches, against the FP64 oracle: the
+eta1-line tile of the transforms and the mass with fewer, as many and more lines
+than threads; the diagonal's launches over blocks of mixed orders; iso-parametric
+launches over more blocks than one launch takes.  Bar: 1e-12 relative in the max
+norm (the results differ from the oracle's by summation order alone)."""
+import numpy as np
+import pytest
+
+from oracle import shp_oracle as O
+from paper_2604_04644_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+
+
+@pytest.fixture(scope="module")
+def shp():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2604_04644_amd import shp as S
+    S.lib()
+    return S
+
+
+def say(msg):
+    print(msg, flush=True)
+
+
+def rel(a, b):
+    return float(np.abs(a - b).max() / max(np.abs(b).max(), 1e-300))
+
+
+def set_curved(shp, plan, b, maps, shape, P):
+    xi, _ = shp.quadrature(shape, P + 2)
+    plan.set_geometry(b, torch.from_numpy(W.jacobian(maps, xi, curved=True)).cuda())
+    return W.jacobian(maps, O.reference_points(shape, P + 2), curved=True)
+
+
+@pytest.mark.parametrize("P", [1, 4, 8, 9, 10])
+def test_values_tile_edges(shp, P):
+    """Two whole tiles and one element over: the default launch (spread to one element
+    a work-group), tiles whose lines fill the threads, and tiles of twice the lines
+    (a second line per thread) give the same bits."""
+    Q2, NT = (P + 2) ** 2, 512 if P >= 9 else 256
+    E = NT // Q2
+    ne = 2 * E + 1
+    for s in O.SHAPES:
+        say(f"[tiles] values P={P} {s} n_elem={ne}")
+        maps = W.shape_batch(s, ne)
+        plan = shp.Plan([(s, P, ne, "curved")])
+        jo = set_curved(shp, plan, 0, maps, s, P)
+        for k, op in enumerate(("bwd", "iprod", "mass")):
+            x = W.point_values(ne, Q2 * (P + 2), 900 + k) if op == "iprod" else W.coeffs(ne, plan.n_modes[0], 900 + k)
+            xt = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+            y = plan.apply(0, op, xt).cpu().numpy()
+            ref = O.apply_op(op, s, P, P + 2, jo, x, chunk=4)
+            assert rel(y.reshape(ref.shape), ref) <= TOL, (s, op)
+            for e in (E, 2 * E):
+                plan.set_tiling(0, op, e, NT, 0)
+                assert np.array_equal(plan.apply(0, op, xt).cpu().numpy(), y), (s, op, e)
+
+
+def test_diag_mixed_orders_many_blocks(shp):
+    """The diagonal of 21 blocks, 17 of them of one order (more than two launches
+    take) and the others of another, from one element up."""
+    say("[tiles] diagonal of 21 blocks")
+    blocks = [(O.SHAPES[i % 4], 2, 1 + 3 * i, "curved") for i in range(17)]
+    blocks += [(s, 3, 5, "curved") for s in O.SHAPES]
+    plan = shp.Plan(blocks)
+    jo = [set_curved(shp, plan, b, W.shape_batch(s, n), s, P) for b, (s, P, n, _) in enumerate(blocks)]
+    d = plan.helmholtz_diag(0.8).cpu().numpy()
+    for b, (s, P, n, _) in enumerate(blocks):
+        co, _ = plan.offsets(b)
+        NP = plan.n_modes[b]
+        ref = np.diagonal(O.Element(s, P, P + 2, jo[b]).helmholtz(0.8), axis1=1, axis2=2)
+        assert rel(d[co:co + n * NP].reshape(n, NP), ref) <= TOL, (b, s)
+
+
+@pytest.mark.parametrize("P,sizes", [(1, (15, 16, 17, 33)), (3, (3, 4, 5, 9)), (4, (1, 2, 3, 5)), (9, (1, 1, 2, 1))])
+def test_iso_many_blocks(shp, P, sizes):
+    """Iso-parametric blocks around a tile's size, 20 of them up to P = 4 (one launch
+    takes 16): the whole mesh equals the blocks and the oracle."""
+    reps = 5 if P <= 4 else 1
+    blocks = [(s, P, n, "isoparam") for _ in range(reps) for s, n in zip(O.SHAPES, sizes)]
+    say(f"[tiles] iso P={P} {len(blocks)} blocks")
+    plan = shp.Plan(blocks)
+    X = []
+    for b, (s, _, n, _) in enumerate(blocks):
+        idx, vxi = O.vertex_modes(s, P)
+        X.append(W.iso_coords(W.shape_batch(s, n), idx, vxi, plan.n_modes[b], 950 + b, curved=True,
+                              amp=0.02 if P <= 4 else 0.004))
+        plan.set_geometry(b, torch.from_numpy(X[b]).cuda())
+    x = W.coeffs(1, plan.totals()[0], 960)[0]
+    y = plan.apply(-1, "helmholtz", torch.from_numpy(x).cuda(), lam=1.1).cpu().numpy()
+    for b, (s, _, n, _) in enumerate(blocks):
+        co, _ = plan.offsets(b)
+        NP = plan.n_modes[b]
+        xb = np.ascontiguousarray(x[co:co + n * NP].reshape(n, NP))
+        yb = plan.apply(b, "helmholtz", torch.from_numpy(xb).cuda(), lam=1.1).cpu().numpy().ravel()
+        assert np.array_equal(yb, y[co:co + n * NP]), (b, s)
+        ref = O.apply_op("helmholtz", s, P, P + 2, O.isoparametric_jacobian(s, P, P + 2, X[b]), xb, lam=1.1, chunk=2)
+        assert rel(yb.reshape(n, NP), ref) <= TOL, (b, s)
