@@ -241,11 +241,16 @@ Tiling default_tiling(int sh, int P, int opk, size_t lds_budget = 40 * 1024) {
   return t;
 }
 
-Tiling iso_tiling(int P) { return Tiling{iso_shape(P).E, iso_shape(P).NT, 2}; }
 size_t iso_lds(int sh, int P) {
   const size_t lds = op_lds_bytes(sh, P, OPK_HELM, iso_shape(P).E, 2);
   // a joint element has three point buffers for each coordinate besides
   return iso_shape(P).joint ? lds + sizeof(double) * 9 * (P + 2) * (P + 2) * qpad(P + 2) : lds;
+}
+
+void iso_add(IsoMesh& m, int blk, int P, long long n_elem) {
+  m.blk[m.nblk] = blk;
+  m.wg0[m.nblk + 1] = m.wg0[m.nblk] + (n_elem + iso_shape(P).E - 1) / iso_shape(P).E;
+  ++m.nblk;
 }
 
 // A launch of n_elem elements with fewer tiles than the chip has CUs takes smaller
@@ -258,7 +263,6 @@ Tiling spread(Tiling t, long long n_elem, int opk) {
 }
 
 Tiling effective(const Tiling& set, int sh, int P, int opk, long long n_elem) {
-  if (opk == OPK_HELM_ISO || opk == OPK_LAP_ISO) return iso_tiling(P);
   if (set.E > 0 && set.NT > 0) return set;
   const Tiling t = default_tiling(sh, P, opk);
   return is_2d(sh) ? t : spread(t, n_elem, opk);
@@ -601,9 +605,10 @@ int shp_plan_set_geometry(shp_plan p, int blk, const double* jac, void* stream) 
     e = hipMemcpyAsync(p->ws + B.off_xco, jac, sizeof(double) * (size_t)B.d.n_elem * 3 * B.NP,
                        hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return dev_fail(e, "coordinate copy");
-    const Tiling t = iso_tiling(B.d.P);
-    e = launch_iso_check(B.d.P, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), blk, t.E,
-                         (B.d.n_elem + t.E - 1) / t.E, t.NT, iso_lds(B.d.shape, B.d.P), status, s);
+    IsoMesh m{};
+    iso_add(m, blk, B.d.P, B.d.n_elem);
+    e = launch_iso_check(B.d.P, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), m,
+                         iso_lds(B.d.shape, B.d.P), status, s);
     if (e != hipSuccess) return dev_fail(e, "iso-parametric geometry check launch");
   } else {
   GeomArgs g;
@@ -811,7 +816,6 @@ static bool mf_mesh(shp_plan p) {
 
 // the default launch shape of the whole-mesh launch of operator opk
 static Tiling default_mixed(shp_plan p, int opk) {
-  if (opk == OPK_HELM_ISO || opk == OPK_LAP_ISO) return iso_tiling(p->blocks[0].d.P);
   const int P0 = p->blocks[0].d.P;
   const bool dim2 = is_2d(p->blocks[0].d.shape);
   if (helm_action(opk) && p->uniform_P && P0 >= 7 && !dim2) {
@@ -849,6 +853,15 @@ constexpr double LPT_WEIGHT[4][10] = {
     {1.03, 1.08, 1.04, 0.99, 1.03, 1.03, 1.08, 1.05, 1.28, 1.65},
     {1.23, 1.11, 1.06, 1.07, 1.07, 1.14, 1.15, 1.58, 1.44, 1.75}};
 
+// the plan's blocks, the costlier shapes first
+static std::vector<int> cost_order(shp_plan p) {
+  std::vector<int> order(p->blocks.size());
+  for (size_t b = 0; b < order.size(); ++b) order[b] = (int)b;
+  auto cost = [&](int b) { return LPT_WEIGHT[p->blocks[b].d.shape][p->blocks[b].d.P - 1]; };
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost(a) > cost(b); });
+  return order;
+}
+
 // Build and upload the whole-mesh tile list of one operator: tiles of E
 // elements from every block, heaviest first (longest-processing-time order).
 static int build_tiles(shp_plan p, int opk, hipStream_t s) {
@@ -856,10 +869,9 @@ static int build_tiles(shp_plan p, int opk, hipStream_t s) {
   const int E = mt.E;
   size_t lds = 0;
   for (const auto& B : p->blocks) {
-    const bool f32 = opk == OPK_HELM_F32 || opk == OPK_LAP_F32, iso = opk == OPK_HELM_ISO || opk == OPK_LAP_ISO;
+    const bool f32 = opk == OPK_HELM_F32 || opk == OPK_LAP_F32;
     lds = std::max(lds, is_2d(B.d.shape) ? lds_bytes_2d(B.d.shape, B.d.P, E, opk, mt.NT)
                         : f32            ? lds_bytes_f32(B.d.shape, B.d.P, E)
-                        : iso            ? iso_lds(B.d.shape, B.d.P)
                                          : op_lds_bytes(B.d.shape, B.d.P, opk, E, opk == OPK_ADR ? 2 : mt.persist));
   }
   struct T2 {
@@ -1015,14 +1027,10 @@ static hipError_t apply_mf(shp_plan p, int blk, int opk, const double* in, doubl
   if (blk >= 0) {
     m.blk[m.nblk++] = mf_block(p, blk, in, out);
   } else {
-    int order[MF_MAX_BLK];
-    for (int b = 0; b < (int)p->blocks.size(); ++b) order[b] = b;
-    auto cost = [&](int b) { return LPT_WEIGHT[p->blocks[b].d.shape][p->blocks[b].d.P - 1]; };
-    std::stable_sort(order, order + p->blocks.size(), [&](int a, int b) { return cost(a) > cost(b); });
-    for (int i = 0; i < (int)p->blocks.size(); ++i) {
-      const Block& B = p->blocks[order[i]];
+    for (int b : cost_order(p)) {
+      const Block& B = p->blocks[b];
       MfBlock& k = m.blk[m.nblk++];
-      k = mf_block(p, order[i], in + B.coeff_off, out + B.coeff_off);
+      k = mf_block(p, b, in + B.coeff_off, out + B.coeff_off);
       if (adv) k.aux = adv + 3 * B.phys_off;
     }
   }
@@ -1144,20 +1152,19 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
         if (!p->blocks[b].geom_ok) return fail(SHP_ERR_STATE, "block %d: geometry not set", b);
       const int iopk = (opk == OPK_HELM) ? OPK_HELM_ISO : OPK_LAP_ISO;
       const BlockStatic* bst = reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat);
-      hipError_t e;
-      if (blk >= 0) {
-        const Block& B = p->blocks[blk];
-        const Tiling t = iso_tiling(B.d.P);
-        e = launch_iso(B.d.P, iopk, bst, nullptr, 0, in, out, lambda, t.NT,
-                       iso_lds(B.d.shape, B.d.P), t.E, blk, (B.d.n_elem + t.E - 1) / t.E, s);
-      } else {
-        if (p->mixed_dirty[iopk])
-          if (int r = build_tiles(p, iopk, s)) return r;
-        const Tiling t = p->mixed_now[iopk];
-        const size_t lds = p->mixed_lds[iopk];
-        const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)iopk * p->max_tiles;
-        e = launch_iso(p->blocks[0].d.P, iopk, bst, tiles, p->mixed_ntiles[iopk], in, out, lambda, t.NT, lds, t.E, -1,
-                       p->mixed_ntiles[iopk], s);
+      // the costlier shapes first, ISO_MAX_BLK blocks to a launch
+      const std::vector<int> order = blk >= 0 ? std::vector<int>{blk} : cost_order(p);
+      hipError_t e = hipSuccess;
+      for (size_t i = 0; i < order.size() && e == hipSuccess;) {
+        IsoMesh m{};
+        m.whole = blk < 0;
+        size_t lds = 0;
+        for (; i < order.size() && m.nblk < ISO_MAX_BLK; ++i) {
+          const Block& B = p->blocks[order[i]];
+          lds = std::max(lds, iso_lds(B.d.shape, B.d.P));
+          iso_add(m, order[i], B.d.P, B.d.n_elem);
+        }
+        e = launch_iso(p->blocks[order[0]].d.P, iopk, bst, m, in, out, lambda, lds, s);
       }
       if (e != hipSuccess) return dev_fail(e, "iso-parametric launch");
       return SHP_OK;

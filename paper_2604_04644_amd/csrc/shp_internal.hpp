@@ -159,13 +159,19 @@ hipError_t launch_mixed(int P, int opk, const BlockStatic* blocks, const Tile* t
                         double* out, long long in_cs, long long out_cs, double lambda, int threads, size_t lds, int E,
                         int persist, hipStream_t s);
 // iso-parametric blocks of one order P: Laplacian/Helmholtz action with the
-// geometry recomputed from coordinates (tile list, or one block's tiles of E
-// elements when blk_only >= 0), and the geometry check of one block
-hipError_t launch_iso(int P, int opk, const BlockStatic* blocks, const Tile* tiles, int ntiles, const double* in,
-                      double* out, double lambda, int threads, size_t lds, int E, int blk_only, long long nwg,
-                      hipStream_t s);
-hipError_t launch_iso_check(int P, const BlockStatic* blocks, int blk, int E, long long nwg, int threads, size_t lds,
-                            int* status, hipStream_t s);
+// geometry recomputed from coordinates, and the geometry check.  Block blk[i] owns the
+// work-groups from wg0[i] on, of iso_shape(P).E elements each in order (an element per
+// work-group at most orders: a list of tiles would be as long as the mesh).
+constexpr int ISO_MAX_BLK = 16;
+struct IsoMesh {
+  int nblk, whole;  // whole: in/out are whole-mesh buffers, else block blk[0]'s
+  int blk[ISO_MAX_BLK];
+  long long wg0[ISO_MAX_BLK + 1];
+};
+hipError_t launch_iso(int P, int opk, const BlockStatic* blocks, const IsoMesh& m, const double* in, double* out,
+                      double lambda, size_t lds, hipStream_t s);
+hipError_t launch_iso_check(int P, const BlockStatic* blocks, const IsoMesh& m, size_t lds, int* status,
+                            hipStream_t s);
 // 2D shapes (quadrilateral, triangle): tables, points, and the launchers
 // (shp_k_2d_*.hip): block launch, whole-mesh launch, geometry, LDS bytes
 void build_tables2d(int sh, int P, int pts, std::vector<double>& tab);

@@ -10,7 +10,9 @@
 // and the collocated derivatives (the stages of the Helmholtz tile), which
 // give d x_c/d eta_d at the points; then per point the determinant, the
 // inverse d eta/d x, jw = w |det| / prod (1 - eta_d)^alpha_d (the reference
-// weight table wref) and g = jw (d eta/d x)(d eta/d x)^T.
+// weight table wref) and g = jw (d eta/d x)(d eta/d x)^T.  Two forms, chosen by order
+// (iso_shape): each coordinate by itself with the factors kept in registers, or the
+// coordinates and the solution together.
 #pragma once
 #include "shp_kernels.hpp"
 
@@ -103,21 +105,19 @@ __device__ __forceinline__ bool iso_geometry(const double* __restrict__ xco, con
   return ok;
 }
 
-// The tile of work-group blockIdx.x: from the tile list, or, with
-// blk_only >= 0, the tiles of E_only elements of that block in order.
-__device__ __forceinline__ bool iso_tile(const BlockStatic* __restrict__ blocks, const Tile* __restrict__ tiles,
-                                         int ntiles, int blk_only, int E_only, Tile& tl) {
-  if (blk_only >= 0) {
-    tl.blk = blk_only;
-    tl.e0 = (long long)blockIdx.x * E_only;
-    const long long rem = blocks[blk_only].n_elem - tl.e0;
-    if (rem <= 0) return false;
-    tl.ne = rem < E_only ? (int)rem : E_only;
-    return true;
-  }
-  if ((int)blockIdx.x >= ntiles) return false;
-  tl = tiles[blockIdx.x];
-  return true;
+// The tile of work-group blockIdx.x.
+template <int P>
+__device__ __forceinline__ Tile iso_tile(const BlockStatic* __restrict__ blocks, const IsoMesh& m) {
+  constexpr int E = iso_shape(P).E;
+  const long long g = blockIdx.x;
+  int i = 0;
+  while (i + 1 < m.nblk && g >= m.wg0[i + 1]) ++i;
+  Tile tl;
+  tl.blk = m.blk[i];
+  tl.e0 = (g - m.wg0[i]) * E;
+  const long long rem = blocks[tl.blk].n_elem - tl.e0;
+  tl.ne = rem < E ? (int)rem : E;
+  return tl;
 }
 
 template <int SH, int P, int OP, int PPT>
@@ -149,7 +149,11 @@ __device__ __forceinline__ void iso_helm(const BlockStatic& b, const Tile& tl, c
 // The three coordinates and the solution are the NF = 4 fields (3 for the geometry
 // check) of one element and run through the forward stages as four "elements" of the
 // tile: a stage has 4 Q^2 line tasks, one per thread, and the work-group waits on 11
-// barriers instead of 28.  A coordinate takes three point buffers, G2 in place of U.
+// barriers instead of 28.  A coordinate takes three point buffers, G2 in place of U:
+// 13 buffers an element against 16 (P = 4, 13.9k elements of mixed shapes: 103.7 us one
+// field after the other, 91 with 16 buffers, 87 with 13).  At P = 4 the LDS is busy 60 %
+// and the FP64 pipes 45 % of the time, 20-28 waves to a CU; padding the fields against
+// bank conflicts changed nothing, 16-byte line accesses cost 4 us.
 
 // the tile of the fields: field c at c * per
 template <int SH, int P>
@@ -321,18 +325,15 @@ __device__ __forceinline__ void iso_action(const BlockStatic& b, const Tile& tl,
 }
 
 // Laplacian (OP = OPK_LAP) or Helmholtz (OPK_HELM) action of iso-parametric
-// blocks of order P, one tile per work-group; in/out are whole-mesh buffers,
-// or one block's buffers when blk_only >= 0.
+// blocks of order P, one tile per work-group.
 template <int P, int OP, int PPT>
-__global__ void __launch_bounds__(iso_shape(P).NT) k_helm_mixed_iso(const BlockStatic* __restrict__ blocks,
-                                                        const Tile* __restrict__ tiles, int ntiles, const double* in,
-                                                        double* out, double lambda, int blk_only, int E_only) {
+__global__ void __launch_bounds__(iso_shape(P).NT) k_helm_iso(const BlockStatic* __restrict__ blocks, IsoMesh m,
+                                                              const double* in, double* out, double lambda) {
   extern __shared__ double smem[];
-  Tile tl;
-  if (!iso_tile(blocks, tiles, ntiles, blk_only, E_only, tl)) return;
+  const Tile tl = iso_tile<P>(blocks, m);
   const BlockStatic b = blocks[tl.blk];
-  const double* bin = in + (blk_only >= 0 ? 0 : b.coeff_off);
-  double* bout = out + (blk_only >= 0 ? 0 : b.coeff_off);
+  const double* bin = in + (m.whole ? b.coeff_off : 0);
+  double* bout = out + (m.whole ? b.coeff_off : 0);
   switch (b.shape) {
     case HEX: iso_action<HEX, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
     case PRISM: iso_action<PRISM, P, OP, PPT>(b, tl, bin, bout, lambda, smem); break;
@@ -353,15 +354,14 @@ __device__ __forceinline__ void iso_check_tile(const BlockStatic& b, const Tile&
   if (!iso_geometry<SH, P, PPT>(b.xco, b.wref, tl.e0, tl.ne, T, g)) atomicOr(status, 1);
 }
 
-// The geometry of block blk's tiles only: status set to 1 when some point has
-// a non-positive determinant or a non-finite factor.
+// The geometry only: status set to 1 when some point has a non-positive determinant or
+// a non-finite factor.
 template <int P, int PPT>
-__global__ void __launch_bounds__(iso_shape(P).NT) k_iso_check(const BlockStatic* __restrict__ blocks, int blk, int E,
-                                                   int* __restrict__ status) {
+__global__ void __launch_bounds__(iso_shape(P).NT) k_iso_check(const BlockStatic* __restrict__ blocks, IsoMesh m,
+                                                               int* __restrict__ status) {
   extern __shared__ double smem[];
-  Tile tl;
-  if (!iso_tile(blocks, nullptr, 0, blk, E, tl)) return;
-  const BlockStatic b = blocks[blk];
+  const Tile tl = iso_tile<P>(blocks, m);
+  const BlockStatic b = blocks[tl.blk];
   switch (b.shape) {
     case HEX: iso_check_tile<HEX, P, PPT>(b, tl, smem, status); break;
     case PRISM: iso_check_tile<PRISM, P, PPT>(b, tl, smem, status); break;
