@@ -262,6 +262,23 @@ Tiling spread(Tiling t, long long n_elem, int opk) {
   return t;
 }
 
+// Whether a launch reads its fields and factors and writes its result with
+// non-temporal accesses.  Data that stay in the 256 MiB Infinity Cache until the next
+// call are better left there; past it they only push each other out.  Transforms and
+// mass: from the size at which a transform and back (values written and read again,
+// weights: 24 bytes a point) exceeds it, 11.2M points.  P = 4 mesh, ordinary /
+// non-temporal, us: bwd + iprod + mass on their own fields 6.5M points 81 / 76, 11.2M
+// 138 / 116, 26.5M 299 / 247; bwd, a pass over its result and iprod 68 / 75, 111 / 109,
+// 270 / 255 (iprod repeated on one field alone: 36 / 41 at 11.2M, 98 / 91 at 26.5M).
+// Derivatives (104 bytes a point) from 4M points: both on their own fields, P = 5,
+// 2.1M 88 / 90, 3.1M 139 / 129, 5.2M 227 / 205, 10.3M 420 / 391; one after the other
+// with a pass between 93 / 115, 147 / 161, 261 / 251, 512 / 477.
+bool streams_nt(int opk, long long n_points) {
+  constexpr long long MIB = 1LL << 20;
+  if (values_op(opk)) return 24 * n_points > 256 * MIB;
+  return (opk == OPK_DERIV || opk == OPK_IPRD) && 104 * n_points > 400 * MIB;
+}
+
 Tiling effective(const Tiling& set, int sh, int P, int opk, long long n_elem) {
   if (set.E > 0 && set.NT > 0) return set;
   const Tiling t = default_tiling(sh, P, opk);
@@ -1056,6 +1073,7 @@ static hipError_t apply_block(shp_plan p, int blk, int opk, const double* in, do
   a.out_cs = cs;
   a.lambda = lambda;
   a.E = t.E;
+  a.nt = streams_nt(opk, B.d.n_elem * (long long)B.NQ);
   return launch_block(B.d.shape, B.d.P, opk, a, t.NT, t.persist, s);
 }
 
@@ -1279,7 +1297,8 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
   const size_t lds = p->mixed_lds[opk];
   const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
   hipError_t e = launch_mixed(p->blocks[0].d.P, opk, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), tiles,
-                              p->mixed_ntiles[opk], in, out, p->total_phys, p->total_phys, lambda, NT, lds, E, mt.persist, s);
+                              p->mixed_ntiles[opk], in, out, p->total_phys, p->total_phys, lambda, NT, lds, E, mt.persist,
+                              streams_nt(opk, p->total_phys), s);
   if (e != hipSuccess) return dev_fail(e, "mixed launch");
   return SHP_OK;
 }

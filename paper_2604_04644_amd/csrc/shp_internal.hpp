@@ -157,7 +157,7 @@ bool mf_helm_shape(int P, int* E, int* NT);
 hipError_t launch_mf_helm(int P, MfMesh& m, double lambda, bool react, hipStream_t s);
 hipError_t launch_mixed(int P, int opk, const BlockStatic* blocks, const Tile* tiles, int ntiles, const double* in,
                         double* out, long long in_cs, long long out_cs, double lambda, int threads, size_t lds, int E,
-                        int persist, hipStream_t s);
+                        int persist, bool nt, hipStream_t s);
 // iso-parametric blocks of one order P: Laplacian/Helmholtz action with the
 // geometry recomputed from coordinates, and the geometry check.  Block blk[i] owns the
 // work-groups from wg0[i] on, of iso_shape(P).E elements each in order (an element per

@@ -298,7 +298,7 @@ hipError_t launch_geometry(int sh, int P, const GeomArgs& g, hipStream_t s) {
 #define D_(p)                                                                                                      \
   hipError_t launch_mixed_P##p(int opk, const BlockStatic* blocks, const Tile* tiles, int ntiles, const double* in, \
                                double* out, long long in_cs, long long out_cs, double lambda, int threads,          \
-                               size_t lds, int E, int persist, hipStream_t s);                                      \
+                               size_t lds, int E, int persist, bool nt, hipStream_t s);                                   \
   hipError_t launch_mixed_f32_P##p(int opk, const BlockStatic* blocks, const Tile* tiles, int ntiles,               \
                                    const float* in, float* out, double lambda, int threads, size_t lds, int E,       \
                                    bool fac32, hipStream_t s);                                                       \
@@ -435,12 +435,12 @@ hipError_t launch_adv_factors(const double* fac, const double* dxi, const double
 
 hipError_t launch_mixed(int P, int opk, const BlockStatic* blocks, const Tile* tiles, int ntiles, const double* in,
                         double* out, long long in_cs, long long out_cs, double lambda, int threads, size_t lds, int E,
-                        int persist, hipStream_t s) {
+                        int persist, bool nt, hipStream_t s) {
   switch (P) {
 #define C_(p)                                                                                                   \
   case p:                                                                                                       \
     return launch_mixed_P##p(opk, blocks, tiles, ntiles, in, out, in_cs, out_cs, lambda, threads, lds, E, persist, \
-                             s);
+                             nt, s);
     C_(1) C_(2) C_(3) C_(4) C_(5) C_(6) C_(7) C_(8) C_(9) C_(10)
 #undef C_
   }

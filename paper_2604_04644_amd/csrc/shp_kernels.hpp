@@ -67,7 +67,7 @@ struct OpArgs {
   long long out_cs;  // component stride of a vector-field output (points)
   double lambda;
   int E;             // elements per tile
-  int pad_;
+  int nt;            // non-temporal streams (transforms, mass, derivatives)
 };
 
 // A tile of a mixed launch: block index, first element, element count.
@@ -748,13 +748,31 @@ __device__ void load_modes(const Tile_<SH, P, R>& T, const R* __restrict__ in, l
   }
 }
 
-template <int SH, int P, typename R>
+// A value that is read or written once by the launch: with NT past the caches' normal
+// replacement, so that a launch whose streams exceed the Infinity Cache does not evict
+// what the next one could still find there (streams_nt in shp_api.cpp has the rule).
+template <bool NT, typename T>
+__device__ __forceinline__ T stream_load(const T* p) {
+  if constexpr (NT)
+    return __builtin_nontemporal_load(p);
+  else
+    return *p;
+}
+template <bool NT, typename T>
+__device__ __forceinline__ void stream_store(T v, T* p) {
+  if constexpr (NT)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
+template <bool NT = false, int SH, int P, typename R>
 __device__ void store_modes(const Tile_<SH, P, R>& T, R* __restrict__ out, long long e0, int ne, int buf) {
   using D = Dims<SH, P>;
   R* dst = out + e0 * D::NP;
   for (int t = tid(); t < ne * D::NP; t += nthr()) {
     const int e = t / D::NP, m = t - e * D::NP;
-    dst[t] = (buf < 0 ? T.U(e) : T.G(e, buf))[m];
+    stream_store<NT>((buf < 0 ? T.U(e) : T.G(e, buf))[m], &dst[t]);
   }
 }
 
@@ -812,7 +830,7 @@ constexpr int values_per() {
   return values_bs<SH, P>() + D::NC * D::QP;
 }
 
-template <int SH, int P, int OP, typename R>
+template <bool NT, int OP, int SH, int P, typename R>
 __device__ void values_tile(const OpArgs& a, long long e0, int ne, const Tile_<SH, P, R>& T) {
   using D = Dims<SH, P>;
   constexpr int Q = D::Q, n = D::n, Q2 = D::Q2, Q3 = D::Q3, QP = D::QP;
@@ -829,10 +847,10 @@ __device__ void values_tile(const OpArgs& a, long long e0, int ne, const Tile_<S
     const int t = tid() < nl ? tid() : nl - 1;
     const int e = t / Q2, jk = t - e * Q2;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) w[i] = fac[e * (NFAC * Q3) + i * Q2 + jk];
+    for (int i = 0; i < Q; ++i) w[i] = stream_load<NT>(&fac[e * (NFAC * Q3) + i * Q2 + jk]);
     if constexpr (OP == OPK_IPR) {
 #pragma unroll
-      for (int i = 0; i < Q; ++i) u[i] = src[e * Q3 + i * Q2 + jk];
+      for (int i = 0; i < Q; ++i) u[i] = stream_load<NT>(&src[e * Q3 + i * Q2 + jk]);
     }
   }
   if constexpr (OP != OPK_IPR) {
@@ -850,10 +868,10 @@ __device__ void values_tile(const OpArgs& a, long long e0, int ne, const Tile_<S
     if constexpr (weighted) {
       if (t != tid()) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) w[i] = fac[e * (NFAC * Q3) + i * Q2 + jk];
+        for (int i = 0; i < Q; ++i) w[i] = stream_load<NT>(&fac[e * (NFAC * Q3) + i * Q2 + jk]);
         if constexpr (OP == OPK_IPR) {
 #pragma unroll
-          for (int i = 0; i < Q; ++i) u[i] = src[e * Q3 + i * Q2 + jk];
+          for (int i = 0; i < Q; ++i) u[i] = stream_load<NT>(&src[e * Q3 + i * Q2 + jk]);
         }
       }
     }
@@ -873,7 +891,7 @@ __device__ void values_tile(const OpArgs& a, long long e0, int ne, const Tile_<S
     if constexpr (OP == OPK_BWD) {
       R* dst = reinterpret_cast<R*>(a.out) + (e0 + e) * Q3 + jk;
 #pragma unroll
-      for (int i = 0; i < Q; ++i) dst[i * Q2] = u[i];
+      for (int i = 0; i < Q; ++i) stream_store<NT>(u[i], &dst[i * Q2]);
     } else {
 #pragma unroll
       for (int i = 0; i < Q; ++i) u[i] = w[i] * u[i];
@@ -893,36 +911,23 @@ __device__ void values_tile(const OpArgs& a, long long e0, int ne, const Tile_<S
     __syncthreads();
     ipr_r<SH, P, false>(T, ne, 0, -1, false);
     __syncthreads();
-    store_modes<SH, P>(T, reinterpret_cast<R*>(a.out), e0, ne, -1);
+    store_modes<NT>(T, reinterpret_cast<R*>(a.out), e0, ne, -1);
   }
 }
 constexpr bool values_op(int op) { return op == OPK_BWD || op == OPK_IPR || op == OPK_MASS; }
 
-// The tile of the other collocated operators: the stages read their tables through
-// the constant path except the tet's eta2 table and the column table, which
-// are all the (compact) LDS head holds.
-template <int SH, int P, int OP, typename R>
-__device__ void tile_body(const OpArgs& a, long long e0, int ne, const Tile_<SH, P, R>& T) {
+// The derivatives at the points, and the inner product with the derivatives.
+template <bool NT, int OP, int SH, int P, typename R>
+__device__ void deriv_tile(const OpArgs& a, long long e0, int ne, const Tile_<SH, P, R>& T) {
   using D = Dims<SH, P>;
   constexpr int Q3 = D::Q3;
-  if constexpr (values_op(OP)) {
-    values_tile<SH, P, OP>(a, e0, ne, T);
-    return;
-  }
   load_tables_helm<SH, P>(a, T);
-  if (OP == OPK_LAP || OP == OPK_HELM) {
-    load_modes<SH, P>(T, reinterpret_cast<const R*>(a.in), e0, ne, 0);
-    __syncthreads();
-    bwd_chain<SH, P>(T, ne);
-  } else {
-    __syncthreads();
-  }
-
-  if (OP == OPK_DERIV) {
+  __syncthreads();
+  if constexpr (OP == OPK_DERIV) {
     const R* src = reinterpret_cast<const R*>(a.in) + e0 * Q3;
     for (int t = tid(); t < ne * Q3; t += nthr()) {
       const int e = t / Q3, pt = t - e * Q3;
-      T.U(e)[lds_pt<SH, P>(pt)] = src[t];
+      T.U(e)[lds_pt<SH, P>(pt)] = stream_load<NT>(&src[t]);
     }
     __syncthreads();
     grad3<SH, P>(T, ne);
@@ -935,28 +940,28 @@ __device__ void tile_body(const OpArgs& a, long long e0, int ne, const Tile_<SH,
       const double* m = dxi + e * (NDXI * Q3) + pt;
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        const double v = m[(0 * 3 + i) * Q3] * g0 + m[(1 * 3 + i) * Q3] * g1 + m[(2 * 3 + i) * Q3] * g2;
-        reinterpret_cast<R*>(a.out)[i * a.out_cs + e0 * Q3 + t] = (R)v;
+        const double v = stream_load<NT>(&m[(0 * 3 + i) * Q3]) * g0 + stream_load<NT>(&m[(1 * 3 + i) * Q3]) * g1 +
+                         stream_load<NT>(&m[(2 * 3 + i) * Q3]) * g2;
+        stream_store<NT>((R)v, &reinterpret_cast<R*>(a.out)[i * a.out_cs + e0 * Q3 + t]);
       }
     }
-    return;
   }
-
-  if (OP == OPK_IPRD) {
+  if constexpr (OP == OPK_IPRD) {
     const double* dxi = a.dxi + e0 * (long long)(NDXI * Q3);
     const double* fac = a.fac + e0 * (long long)(NFAC * Q3);
     for (int t = tid(); t < ne * Q3; t += nthr()) {
       const int e = t / Q3, pt = t - e * Q3;
       const int lp = lds_pt<SH, P>(pt);
       const R* fin = reinterpret_cast<const R*>(a.in);
-      const double f0 = fin[0 * a.in_cs + e0 * Q3 + t];
-      const double f1 = fin[1 * a.in_cs + e0 * Q3 + t];
-      const double f2 = fin[2 * a.in_cs + e0 * Q3 + t];
-      const double jw = fac[e * (NFAC * Q3) + pt];
+      const double f0 = stream_load<NT>(&fin[0 * a.in_cs + e0 * Q3 + t]);
+      const double f1 = stream_load<NT>(&fin[1 * a.in_cs + e0 * Q3 + t]);
+      const double f2 = stream_load<NT>(&fin[2 * a.in_cs + e0 * Q3 + t]);
+      const double jw = stream_load<NT>(&fac[e * (NFAC * Q3) + pt]);
       const double* m = dxi + e * (NDXI * Q3) + pt;
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        const double v = m[(d * 3 + 0) * Q3] * f0 + m[(d * 3 + 1) * Q3] * f1 + m[(d * 3 + 2) * Q3] * f2;
+        const double v = stream_load<NT>(&m[(d * 3 + 0) * Q3]) * f0 + stream_load<NT>(&m[(d * 3 + 1) * Q3]) * f1 +
+                         stream_load<NT>(&m[(d * 3 + 2) * Q3]) * f2;
         T.G(e, d)[lp] = jw * v;
       }
     }
@@ -964,10 +969,39 @@ __device__ void tile_body(const OpArgs& a, long long e0, int ne, const Tile_<SH,
     grad3T<SH, P>(T, ne);
     __syncthreads();
     ipr_chain<SH, P>(T, ne, 2 | 4 | 8);
-    store_modes<SH, P>(T, reinterpret_cast<R*>(a.out), e0, ne, 1);
+    store_modes<NT>(T, reinterpret_cast<R*>(a.out), e0, ne, 1);
+  }
+}
+
+// The tile of the other collocated operators: the stages read their tables through
+// the constant path except the tet's eta2 table and the column table, which
+// are all the (compact) LDS head holds.
+template <int SH, int P, int OP, typename R>
+__device__ void tile_body(const OpArgs& a, long long e0, int ne, const Tile_<SH, P, R>& T) {
+  using D = Dims<SH, P>;
+  constexpr int Q3 = D::Q3;
+  // (hipcc 7.2 cannot compile the whole-mesh kernel of P = 10 with both forms in it:
+  // that order keeps ordinary accesses)
+  if constexpr (values_op(OP)) {
+    if (P < 10 && a.nt)
+      values_tile<true, OP>(a, e0, ne, T);
+    else
+      values_tile<false, OP>(a, e0, ne, T);
     return;
   }
-
+  if constexpr (OP == OPK_DERIV || OP == OPK_IPRD) {
+    if (P < 10 && a.nt)
+      deriv_tile<true, OP>(a, e0, ne, T);
+    else
+      deriv_tile<false, OP>(a, e0, ne, T);
+    return;
+  }
+  load_tables_helm<SH, P>(a, T);
+  if (OP == OPK_LAP || OP == OPK_HELM) {
+    load_modes<SH, P>(T, reinterpret_cast<const R*>(a.in), e0, ne, 0);
+    __syncthreads();
+    bwd_chain<SH, P>(T, ne);
+  }
   if (OP == OPK_LAP || OP == OPK_HELM) {
     grad3<SH, P>(T, ne);
     __syncthreads();
@@ -994,7 +1028,7 @@ __device__ void tile_body(const OpArgs& a, long long e0, int ne, const Tile_<SH,
     grad3T<SH, P>(T, ne);
     __syncthreads();
     ipr_chain<SH, P>(T, ne, (OP == OPK_HELM ? 1 : 0) | 2 | 4 | 8);
-    store_modes<SH, P>(T, reinterpret_cast<R*>(a.out), e0, ne, 1);
+    store_modes<false>(T, reinterpret_cast<R*>(a.out), e0, ne, 1);
     return;
   }
 }
@@ -1109,7 +1143,7 @@ __global__ void __launch_bounds__(512) k_block(OpArgs a) {
 template <int P, int OP>
 __global__ void __launch_bounds__(512) k_mixed(const BlockStatic* __restrict__ blocks, const Tile* __restrict__ tiles,
                                                int ntiles, const double* in, double* out, long long in_cs,
-                                               long long out_cs, double lambda) {
+                                               long long out_cs, double lambda, int nt) {
   extern __shared__ double smem[];
   const int ti = blockIdx.x;
   if (ti >= ntiles) return;
@@ -1130,7 +1164,7 @@ __global__ void __launch_bounds__(512) k_mixed(const BlockStatic* __restrict__ b
   a.out_cs = out_cs;
   a.lambda = lambda;
   a.E = b.E;
-  a.pad_ = 0;
+  a.nt = nt;
   switch (b.shape) {
     case HEX: tile_body<HEX, P, OP>(a, tl.e0, tl.ne, make_tile_op<HEX, P, OP, double>(smem, a.tab)); break;
     case PRISM: tile_body<PRISM, P, OP>(a, tl.e0, tl.ne, make_tile_op<PRISM, P, OP, double>(smem, a.tab)); break;
@@ -1284,7 +1318,7 @@ __device__ void helm_tile(const OpArgs& a, long long e0, int ne, const Tile_<SH,
   __syncthreads();
   ipr_r<SH, P, false>(T, ne, 0, 1, false);
   __syncthreads();
-  store_modes<SH, P>(T, reinterpret_cast<R*>(a.out), e0, ne, 1);
+  store_modes<false>(T, reinterpret_cast<R*>(a.out), e0, ne, 1);
 }
 
 template <int SH, int P, int OP, int PPT>
@@ -1340,7 +1374,7 @@ __global__ void __launch_bounds__(512) k_helm_mixed_persist(const BlockStatic* _
     a.out_cs = 0;
     a.lambda = lambda;
     a.E = 0;
-    a.pad_ = 0;
+    a.nt = 0;
     const bool tables = (tl.blk != prev);
     auto next = [&]() {
       if (nx < ntiles) prefetch_geo<P, PPT>(blocks[tn.blk].fac, tn.e0, tn.ne, g);
@@ -1397,7 +1431,7 @@ __global__ void __launch_bounds__(512) k_helm_mixed_pf(const BlockStatic* __rest
   a.out_cs = 0;
   a.lambda = lambda;
   a.E = 0;
-  a.pad_ = 0;
+  a.nt = 0;
   const R* gt = sizeof(R) == sizeof(double) ? reinterpret_cast<const R*>(b.tab) : reinterpret_cast<const R*>(b.tabf);
   const G* gf;
   if constexpr (sizeof(G) == sizeof(double))
@@ -1447,7 +1481,7 @@ __global__ void __launch_bounds__(512) k_adr_mixed_pf(const BlockStatic* __restr
   a.out_cs = 0;
   a.lambda = lambda;
   a.E = 0;
-  a.pad_ = 0;
+  a.nt = 0;
   const double* ab = adv + 3 * b.phys_off;
   auto none = []() {};
   auto pf = [&]() { prefetch_geo<P, PPT>(b.fac, tl.e0, tl.ne, g); };
@@ -1664,7 +1698,7 @@ __device__ void helm_fused_tile(const OpArgs& a, long long e0, int ne, const Til
   __syncthreads();
   ipr_r<SH, P, false>(T, ne, 0, 1, false);  // -> modes in G1
   __syncthreads();
-  store_modes<SH, P>(T, a.out, e0, ne, 1);
+  store_modes<false>(T, a.out, e0, ne, 1);
 }
 
 template <int SH, int P, int OP, bool PF>
@@ -1698,7 +1732,7 @@ __global__ void __launch_bounds__(512) k_helm_fused_mixed(const BlockStatic* __r
   a.out_cs = 0;
   a.lambda = lambda;
   a.E = 0;
-  a.pad_ = 0;
+  a.nt = 0;
   switch (b.shape) {
     case HEX: helm_fused_tile<HEX, P, OP, PF>(a, tl.e0, tl.ne, make_tile3<HEX, P>(smem, a.tab), true); break;
     case PRISM: helm_fused_tile<PRISM, P, OP, PF>(a, tl.e0, tl.ne, make_tile3<PRISM, P>(smem, a.tab), true); break;
@@ -1940,7 +1974,7 @@ __device__ void helm_nc_tile(const OpArgs& a, long long e0, int ne, const Tile_<
   __syncthreads();
   nc_ipr_r<SH, P>(T, ne, 0, 1, -1);  // y = C3^T K + dC3^T K3 -> B0
   __syncthreads();
-  store_modes<SH, P>(T, a.out, e0, ne, -1);
+  store_modes<false>(T, a.out, e0, ne, -1);
 }
 
 template <int SH, int P, int OP>
@@ -1974,7 +2008,7 @@ __global__ void __launch_bounds__(512) k_helm_nc_mixed(const BlockStatic* __rest
   a.out_cs = 0;
   a.lambda = lambda;
   a.E = 0;
-  a.pad_ = 0;
+  a.nt = 0;
   switch (b.shape) {
     case HEX: helm_nc_tile<HEX, P, OP>(a, tl.e0, tl.ne, make_tile5<HEX, P>(smem, a.tab)); break;
     case PRISM: helm_nc_tile<PRISM, P, OP>(a, tl.e0, tl.ne, make_tile5<PRISM, P>(smem, a.tab)); break;

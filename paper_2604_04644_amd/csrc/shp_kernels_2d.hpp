@@ -392,7 +392,7 @@ __global__ void __launch_bounds__(512) k_mixed2d(const BlockStatic* __restrict__
   a.out_cs = out_cs;
   a.lambda = lambda;
   a.E = 0;
-  a.pad_ = 0;
+  a.nt = 0;
   if (b.shape == QUAD)
     tile2d<QUAD, P, OP>(a, tl.e0, tl.ne, make_tile2<QUAD, P>(smem));
   else
@@ -703,7 +703,7 @@ __global__ void __launch_bounds__(512) k_helm_mixed2d(const BlockStatic* __restr
   a.out_cs = 0;
   a.lambda = lambda;
   a.E = 0;
-  a.pad_ = 0;
+  a.nt = 0;
   if (b.shape == QUAD)
     helm2d_tile<QUAD, P, OP, PPT>(a, tl.e0, tl.ne, make_tile2h<QUAD, P>(smem));
   else

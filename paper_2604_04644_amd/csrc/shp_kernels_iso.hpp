@@ -135,7 +135,7 @@ __device__ __forceinline__ void iso_helm(const BlockStatic& b, const Tile& tl, c
   a.out_cs = 0;
   a.lambda = lambda;
   a.E = 0;
-  a.pad_ = 0;
+  a.nt = 0;
   const Tile_<SH, P> T = make_tile_h<SH, P, double>(smem, b.tab);
   load_tables_helm<SH, P>(a, T);
   GeoRegs<PPT> g;
@@ -294,7 +294,7 @@ __device__ __forceinline__ void iso_joint(const BlockStatic& b, const Tile& tl, 
   __syncthreads();
   ipr_r<SH, P, false>(S, 1, 0, 1, false);
   __syncthreads();
-  store_modes<SH, P>(S, out, tl.e0, 1, 1);
+  store_modes<false>(S, out, tl.e0, 1, 1);
 }
 
 template <int SH, int P>

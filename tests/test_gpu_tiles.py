@@ -102,3 +102,34 @@ def test_iso_many_blocks(shp, P, sizes):
         assert np.array_equal(yb, y[co:co + n * NP]), (b, s)
         ref = O.apply_op("helmholtz", s, P, P + 2, O.isoparametric_jacobian(s, P, P + 2, X[b]), xb, lam=1.1, chunk=2)
         assert rel(yb.reshape(n, NP), ref) <= TOL, (b, s)
+
+
+def test_streamed_launches(shp):
+    """Launches whose streams exceed the Infinity Cache (11.34 million points; affine
+    elements, P = 1) read and write past it: the last 29 elements have the bits of a
+    launch of their own, and agree with the oracle."""
+    P, ne, nb = 1, 420_011, 29
+    s, Q3 = "tet", 27
+    say(f"[tiles] streamed launches n_elem={ne}")
+    maps = W.shape_batch(s, ne)
+    last = maps.take(np.arange(ne - nb, ne))
+    big, small = shp.Plan([(s, P, ne, "affine")]), shp.Plan([(s, P, nb, "affine")])
+    big.set_geometry(0, torch.from_numpy(W.affine_jacobian(maps)).cuda())
+    small.set_geometry(0, torch.from_numpy(W.affine_jacobian(last)).cuda())
+    for k, op in enumerate(("bwd", "iprod", "mass", "physderiv", "iprod_deriv")):
+        if op in ("iprod", "physderiv"):
+            x = W.point_values(ne, Q3, 970 + k)
+        elif op == "iprod_deriv":
+            x = W.point_values(ne, Q3, 970 + k, ncomp=3)
+        else:
+            x = W.coeffs(ne, 4, 970 + k)
+        xb = np.ascontiguousarray(x[:, -nb:] if op == "iprod_deriv" else x[-nb:])
+        xt = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+        yb = small.apply(0, op, torch.from_numpy(xb).cuda()).cpu().numpy()
+        ref = O.apply_op(op, s, P, P + 2, W.affine_jacobian(last), xb)
+        assert rel(yb.reshape(ref.shape), ref) <= TOL, op
+        for blk in (0, -1):
+            y = big.apply(blk, op, xt if blk == 0 else xt.reshape((3, -1) if op == "iprod_deriv" else (-1,)))
+            y = y.reshape((3, ne, Q3) if op == "physderiv" else (ne, -1)).cpu().numpy()
+            tail = y[:, -nb:] if op == "physderiv" else y[-nb:]
+            assert np.array_equal(tail.reshape(yb.shape), yb), (op, blk)
