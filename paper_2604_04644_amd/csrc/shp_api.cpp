@@ -174,6 +174,9 @@ bool out_is_modes(int opk) { return !(opk == OPK_BWD || opk == OPK_DERIV || opk 
 // that 4 geometry slots per thread hold the tile's points, and two elements
 // per work-group at P = 7 and 8.  Per shape (hex, prism, pyramid, tet) and
 // P = 7..10: elements per work-group, threads.
+// At P = 2, 6, 9 and 10 the FP64 launch of the default shape is the matrix-core tile's
+// (mf_block_runs, mf_mesh_runs); these are the shapes of the FP32 actions there, and
+// what the shape query reports.
 constexpr int HI_E[4][4] = {{1, 2, 1, 1}, {2, 2, 1, 1}, {2, 2, 1, 1}, {2, 1, 1, 1}};
 constexpr int HI_NT[4][4] = {{256, 512, 512, 512}, {512, 512, 512, 512}, {512, 512, 512, 512}, {512, 256, 512, 512}};
 // the whole-mesh launch at P = 7..10 (one launch shape for every block)
