@@ -252,8 +252,9 @@ size_t iso_lds(int sh, int P) {
 
 void iso_add(IsoMesh& m, int blk, int P, long long n_elem) {
   m.blk[m.nblk] = blk;
-  m.wg0[m.nblk + 1] = m.wg0[m.nblk] + (n_elem + iso_shape(P).E - 1) / iso_shape(P).E;
+  const long long end = m.wg0[m.nblk] + (n_elem + iso_shape(P).E - 1) / iso_shape(P).E;
   ++m.nblk;
+  for (int i = m.nblk; i <= ISO_MAX_BLK; ++i) m.wg0[i] = end;  // no work-group is past the last block
 }
 
 // A launch of n_elem elements with fewer tiles than the chip has CUs takes smaller

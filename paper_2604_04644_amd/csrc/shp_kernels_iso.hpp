@@ -105,18 +105,25 @@ __device__ __forceinline__ bool iso_geometry(const double* __restrict__ xco, con
   return ok;
 }
 
-// The tile of work-group blockIdx.x.
-template <int P>
-__device__ __forceinline__ Tile iso_tile(const BlockStatic* __restrict__ blocks, const IsoMesh& m) {
-  constexpr int E = iso_shape(P).E;
-  const long long g = blockIdx.x;
+// The block of work-group blockIdx.x, as an index into m: every offset is compared, so
+// that they load together, in 32 bits (a grid is smaller), so that the scalar unit does
+// it and the block's pointers stay in scalar registers.
+__device__ __forceinline__ int iso_block(const IsoMesh& m) {
   int i = 0;
-  while (i + 1 < m.nblk && g >= m.wg0[i + 1]) ++i;
+#pragma unroll
+  for (int j = 1; j < ISO_MAX_BLK; ++j) i += blockIdx.x >= (unsigned)m.wg0[j] ? 1 : 0;
+  return __builtin_amdgcn_readfirstlane(i);
+}
+
+// the tile of the work-group, whose block is b
+template <int P>
+__device__ __forceinline__ Tile iso_tile(const BlockStatic& b, const IsoMesh& m, int i) {
+  constexpr int E = iso_shape(P).E;
   Tile tl;
   tl.blk = m.blk[i];
-  tl.e0 = (g - m.wg0[i]) * E;
-  const long long rem = blocks[tl.blk].n_elem - tl.e0;
-  tl.ne = rem < E ? (int)rem : E;
+  tl.e0 = (blockIdx.x - m.wg0[i]) * E;
+  const long long rem = b.n_elem - tl.e0;
+  tl.ne = E == 1 ? 1 : rem < E ? (int)rem : E;
   return tl;
 }
 
@@ -324,14 +331,19 @@ __device__ __forceinline__ void iso_action(const BlockStatic& b, const Tile& tl,
     iso_helm<SH, P, OP, PPT>(b, tl, in, out, lambda, smem);
 }
 
+// One field after the other, the kernels keep the register bound of 512 threads, though
+// they run on 256 up to P = 3 (41.1 us at either bound, P = 1, 73k elements).
+constexpr int iso_bounds(int P) { return iso_shape(P).joint ? iso_shape(P).NT : 512; }
+
 // Laplacian (OP = OPK_LAP) or Helmholtz (OPK_HELM) action of iso-parametric
 // blocks of order P, one tile per work-group.
 template <int P, int OP, int PPT>
-__global__ void __launch_bounds__(iso_shape(P).NT) k_helm_iso(const BlockStatic* __restrict__ blocks, IsoMesh m,
+__global__ void __launch_bounds__(iso_bounds(P)) k_helm_iso(const BlockStatic* __restrict__ blocks, IsoMesh m,
                                                               const double* in, double* out, double lambda) {
   extern __shared__ double smem[];
-  const Tile tl = iso_tile<P>(blocks, m);
-  const BlockStatic b = blocks[tl.blk];
+  const int i = iso_block(m);
+  const BlockStatic b = blocks[m.blk[i]];
+  const Tile tl = iso_tile<P>(b, m, i);
   const double* bin = in + (m.whole ? b.coeff_off : 0);
   double* bout = out + (m.whole ? b.coeff_off : 0);
   switch (b.shape) {
@@ -357,11 +369,12 @@ __device__ __forceinline__ void iso_check_tile(const BlockStatic& b, const Tile&
 // The geometry only: status set to 1 when some point has a non-positive determinant or
 // a non-finite factor.
 template <int P, int PPT>
-__global__ void __launch_bounds__(iso_shape(P).NT) k_iso_check(const BlockStatic* __restrict__ blocks, IsoMesh m,
+__global__ void __launch_bounds__(iso_bounds(P)) k_iso_check(const BlockStatic* __restrict__ blocks, IsoMesh m,
                                                                int* __restrict__ status) {
   extern __shared__ double smem[];
-  const Tile tl = iso_tile<P>(blocks, m);
-  const BlockStatic b = blocks[tl.blk];
+  const int i = iso_block(m);
+  const BlockStatic b = blocks[m.blk[i]];
+  const Tile tl = iso_tile<P>(b, m, i);
   switch (b.shape) {
     case HEX: iso_check_tile<HEX, P, PPT>(b, tl, smem, status); break;
     case PRISM: iso_check_tile<PRISM, P, PPT>(b, tl, smem, status); break;

@@ -134,14 +134,15 @@ constexpr int NDXI = 9;
 // together, us: P = 1 65 / 65, 2 67 / 87, 3 77 / 83, 4 104 / 87, 5 143 / 92, 6 119 / 118,
 // 7 200 / 114, 8 182 / 169, 9 180 / 158; at P = 10 the 13 buffers exceed the LDS.  One
 // after the other, elements fill 512 points, so that a thread keeps the geometry of at
-// most 2 points (4 at P = 10).  Together, the threads cover the 4 Q^2 lines; at P = 4 192
+// most 2 points (4 at P = 10; P = 1, 73k elements, 14 / 16 / 18 / 28 a work-group: 42.1 /
+// 41.4 / 39.1 / 41.1 us).  Together, the threads cover the 4 Q^2 lines; at P = 4 192
 // threads take 88 us, 320 124; two elements with 16 buffers 100-106.
 struct IsoShape {
   int E, NT;
   bool joint;
 };
 constexpr IsoShape iso_shape(int P) {
-  constexpr int E[10] = {16, 8, 4, 1, 1, 1, 1, 1, 1, 1};
+  constexpr int E[10] = {18, 8, 4, 1, 1, 1, 1, 1, 1, 1};
   constexpr int NT[10] = {256, 256, 256, 256, 256, 256, 384, 448, 512, 512};
   return IsoShape{E[P - 1], NT[P - 1], P >= 4 && P <= 9};
 }

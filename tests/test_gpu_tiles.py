@@ -78,7 +78,7 @@ def test_diag_mixed_orders_many_blocks(shp):
         assert rel(d[co:co + n * NP].reshape(n, NP), ref) <= TOL, (b, s)
 
 
-@pytest.mark.parametrize("P,sizes", [(1, (15, 16, 17, 33)), (3, (3, 4, 5, 9)), (4, (1, 2, 3, 5)), (9, (1, 1, 2, 1))])
+@pytest.mark.parametrize("P,sizes", [(1, (17, 18, 19, 37)), (3, (3, 4, 5, 9)), (4, (1, 2, 3, 5)), (9, (1, 1, 2, 1))])
 def test_iso_many_blocks(shp, P, sizes):
     """Iso-parametric blocks around a tile's size, 20 of them up to P = 4 (one launch
     takes 16): the whole mesh equals the blocks and the oracle."""
