@@ -259,11 +259,13 @@ void iso_add(IsoMesh& m, int blk, int P, long long n_elem) {
 
 // A launch of n_elem elements with fewer tiles than the chip has CUs takes smaller
 // ones (the transforms and the mass, whose tiles hold the most elements: 116
-// elements at P = 10, bwd + iprod + mass 34.8 us with 3 per work-group, 31 with 1).
+// elements at P = 10, bwd + iprod + mass 34.8 us with 3 per work-group, 31 with 1), of
+// 512 threads: the eta3 families of stage r are dealt to more waves (60 elements,
+// 256 / 512 threads, mass at P = 4 6.0 / 5.7 us, 6 8.1 / 7.4, 8 10.9 / 9.7).
 Tiling spread(Tiling t, long long n_elem, int opk) {
   constexpr int CUS = 256;
-  if (values_op(opk) && n_elem < (long long)CUS * t.E) t.E = (int)std::max<long long>(1, (n_elem + CUS - 1) / CUS);
-  return t;
+  if (!values_op(opk) || n_elem >= (long long)CUS * t.E) return t;
+  return Tiling{(int)std::max<long long>(1, (n_elem + CUS - 1) / CUS), 512, t.persist};
 }
 
 // Whether a launch reads its fields and factors and writes its result with
