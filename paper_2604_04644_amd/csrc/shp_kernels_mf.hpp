@@ -234,11 +234,12 @@ __device__ __forceinline__ void stage_rT(const V& T, const Lane& w, int fb, int 
           for (int g = 0; g < D::KQ; ++g) s0[g] += s1[g];
         }
         const double* v1 = T.tab + D::oC + D::Q + w.lr;
+        // only row 1 takes the sum (zeros in the other rows of the table would make
+        // an overflowed s0 NaN there)
+        double a1 = acc[0];
 #pragma unroll
-        for (int g = 0; g < D::KQ; ++g) {
-          const double v = v1[4 * g];
-          acc[0] = mma(w.li == 1 ? v : 0.0, s0[g], acc[0]);
-        }
+        for (int g = 0; g < D::KQ; ++g) a1 = mma(v1[4 * g], s0[g], a1);
+        acc[0] = w.lr == 1 ? a1 : acc[0];
       }
       store_rows<RL, 1>(T.el + e * V::PER + yb + (pk >> 8), w, acc, l0 < nl);
     }
@@ -330,11 +331,10 @@ __device__ __forceinline__ void stage_qT_tet(const V& T, const Lane& w, int gb, 
         // adjoint of the extra eta2 term: column (0, 1) also collects v1 * G[1]
         load_rows<D::Q, D::SJ>(G + D::SI, w, b);
         const double* v1 = T.tab + D::oB + D::Q + w.lr;
+        double a1 = acc[0];  // row 1 alone takes it, as in stage_rT
 #pragma unroll
-        for (int g = 0; g < D::KQ; ++g) {
-          const double v = v1[4 * g];
-          acc[0] = mma(w.li == 1 ? v : 0.0, b[g], acc[0]);
-        }
+        for (int g = 0; g < D::KQ; ++g) a1 = mma(v1[4 * g], b[g], a1);
+        acc[0] = w.lr == 1 ? a1 : acc[0];
       }
       store_rows<NQ, D::SJ>(T.el + e * V::PER + fb + col_base(TET, P, PP) * D::SJ + k, w, acc, l0 < nl);
     }

@@ -80,3 +80,31 @@ def test_helm_mesh(shp, P, nblk):
             xb = x[co:co + n * plan.n_modes[b]].clone()
             plan.set_tiling(b, "helmholtz", 1, 64, 0)
             assert torch.equal(plan.apply(b, "helmholtz", xb, lam=1.1).reshape(-1), y[co:co + n * plan.n_modes[b]]), b
+
+
+@pytest.mark.parametrize("P,n", [(2, 11), (6, 3), (9, 2), (10, 2)])
+@pytest.mark.parametrize("shape", O.SHAPES)
+def test_helm_not_finite(shp, shape, P, n):
+    """A NaN, and sums that overflow (the reaction term of a positive constant in one
+    element), stay in their element of a tile, and an overflow reaches the same modes,
+    with the same infinities and NaN, as in the thread-per-line tile."""
+    print(f"[mf] not finite {shape} P={P} n={n}", flush=True)
+    plan, _ = plan_of(shp, [(shape, n)], P)
+    x = W.coeffs(n, plan.n_modes[0], 40 + P)
+    k, rest = n // 2, np.arange(n) != n // 2
+    for lam, bad in ((0.8, np.nan), (1e288, 1e20), (1e290, 1e20), (1e292, 1e20), (1e300, 1e20)):
+        xb = x.copy()
+        if np.isnan(bad):
+            xb[k, 1] = bad
+        else:
+            xb[k] = 0.0
+            xb[k, O.vertex_modes(shape, P)[0]] = bad
+        xt = torch.from_numpy(xb).cuda()
+        plan.set_tiling(0, "helmholtz", 0, 0, 0)
+        y = plan.apply(0, "helmholtz", xt, lam=lam).cpu().numpy()
+        ok = plan.apply(0, "helmholtz", torch.from_numpy(x).cuda(), lam=lam).cpu().numpy()
+        plan.set_tiling(0, "helmholtz", 1, 64, 0)
+        line = plan.apply(0, "helmholtz", xt, lam=lam).cpu().numpy()
+        assert np.isfinite(ok).all() and np.array_equal(y[rest], ok[rest])
+        assert np.array_equal(y, line, equal_nan=True), lam
+        assert not (lam < 1.0 or lam == 1e300) or not np.isfinite(y[k]).any()
