@@ -102,7 +102,7 @@ struct shp_plan_s {
   Tiling mixed[OPK_COUNT];
   int mixed_ntiles[OPK_COUNT] = {};
   Tiling mixed_now[OPK_COUNT];        // launch shape and LDS that go with the tile list (build_tiles)
-  size_t mixed_lds[OPK_COUNT] = {};
+  size_t mixed_lds[OPK_COUNT] = {}, mixed_lds32[OPK_COUNT] = {};  // FP64 and FP32 actions
   bool mixed_dirty[OPK_COUNT] = {};
   bool uniform_P = true;
   int auto_mixed[7] = {2, 2, 2, 2, 2, 2, 2};
@@ -183,10 +183,8 @@ constexpr int HI_NT[4][4] = {{256, 512, 512, 512}, {512, 512, 512, 512}, {512, 5
 constexpr int HI_MESH_E[4] = {2, 1, 1, 1};
 constexpr int HI_MESH_NT[4] = {512, 256, 512, 512};
 
-// the collocated Laplacian / Helmholtz actions: FP64 ones that the matrix-core
-// launch can take, and all of them
-bool mf_action(int opk) { return opk == OPK_HELM || opk == OPK_LAP || opk == OPK_ADR; }
-bool helm_action(int opk) { return mf_action(opk) || opk == OPK_HELM_F32 || opk == OPK_LAP_F32; }
+// the collocated Laplacian / Helmholtz actions
+bool helm_action(int opk) { return opk == OPK_HELM || opk == OPK_LAP || opk == OPK_ADR; }
 
 Tiling default_tiling(int sh, int P, int opk, size_t lds_budget = 40 * 1024) {
   Tiling t;
@@ -238,7 +236,7 @@ Tiling default_tiling(int sh, int P, int opk, size_t lds_budget = 40 * 1024) {
     return t;
   }
   int E = 1;
-  while (E < 16 && op_lds_bytes(sh, P, helm ? (int)OPK_HELM : opk, E + 1, 2) <= lds_budget && (!helm || (E + 1) * Q3 <= 4LL * t.NT)) ++E;
+  while (E < 16 && op_lds_bytes(sh, P, opk, E + 1, 2) <= lds_budget && (!helm || (E + 1) * Q3 <= 4LL * t.NT)) ++E;
   t.E = E;
   t.persist = points_per_thread((long long)E * (P + 2) * (P + 2) * (P + 2), t.NT) > 0 ? 2 : 0;
   return t;
@@ -753,20 +751,12 @@ int shp_block_offsets(shp_plan p, int blk, int64_t* coeff_off, int64_t* phys_off
   return SHP_OK;
 }
 
-// the tile lists of whole-mesh operator opk (and of the FP32 actions that
-// follow its launch shape) no longer hold
-static void drop_tiles(shp_plan p, int opk) {
-  p->mixed_dirty[opk] = true;
-  if (opk == OPK_HELM) p->mixed_dirty[OPK_HELM_F32] = true;
-  if (opk == OPK_LAP) p->mixed_dirty[OPK_LAP_F32] = true;
-}
-
 static void set_tiling_raw(shp_plan p, int blk, int opk, const Tiling& t) {
   if (blk >= 0)
     p->blocks[blk].tiling[opk] = t;
   else {
     p->mixed[opk] = t;
-    drop_tiles(p, opk);
+    p->mixed_dirty[opk] = true;
   }
 }
 
@@ -861,8 +851,7 @@ static Tiling default_mixed(shp_plan p, int opk) {
 }
 
 static Tiling mixed_tiling(shp_plan p, int opk) {
-  // the FP32 actions follow the FP64 action's launch shape when one is set
-  const Tiling t = p->mixed[opk == OPK_HELM_F32 ? (int)OPK_HELM : opk == OPK_LAP_F32 ? (int)OPK_LAP : opk];
+  const Tiling t = p->mixed[opk];
   return t.E > 0 && t.NT > 0 ? t : default_mixed(p, opk);
 }
 
@@ -887,39 +876,44 @@ static std::vector<int> cost_order(shp_plan p) {
 
 // Build and upload the whole-mesh tile list of one operator: tiles of E
 // elements from every block, heaviest first (longest-processing-time order).
+// The FP32 actions run the list and the launch shape of the FP64 ones.
 static int build_tiles(shp_plan p, int opk, hipStream_t s) {
   const Tiling mt = mixed_tiling(p, opk);
   const int E = mt.E;
-  size_t lds = 0;
-  for (const auto& B : p->blocks) {
-    const bool f32 = opk == OPK_HELM_F32 || opk == OPK_LAP_F32;
-    lds = std::max(lds, is_2d(B.d.shape) ? lds_bytes_2d(B.d.shape, B.d.P, E, opk, mt.NT)
-                        : f32            ? lds_bytes_f32(B.d.shape, B.d.P, E)
-                                         : op_lds_bytes(B.d.shape, B.d.P, opk, E, opk == OPK_ADR ? 2 : mt.persist));
-  }
-  struct T2 {
-    Tile t;
+  size_t lds = 0, lds32 = 0;
+  // a block's whole tiles and its last, smaller one: runs of equal cost, so that
+  // the runs are sorted and not the tiles (up to one an element)
+  struct Run {
+    int blk, ne;
+    long long e0, n;
     double cost;
   };
-  std::vector<T2> tl;
+  std::vector<Run> runs;
+  long long ntiles = 0;
   for (int b = 0; b < (int)p->blocks.size(); ++b) {
     const Block& B = p->blocks[b];
+    lds = std::max(lds, is_2d(B.d.shape) ? lds_bytes_2d(B.d.shape, B.d.P, E, opk, mt.NT)
+                                         : op_lds_bytes(B.d.shape, B.d.P, opk, E, opk == OPK_ADR ? 2 : mt.persist));
+    if (!is_2d(B.d.shape)) lds32 = std::max(lds32, lds_bytes_f32(B.d.shape, B.d.P, E));
     // per-element cost weight: the measured Helmholtz launch time per element
     // of the shape relative to the hexahedron at the same P
     const double w = is_2d(B.d.shape) ? 1.0 : LPT_WEIGHT[B.d.shape][B.d.P - 1];
-    for (long long e0 = 0; e0 < B.d.n_elem; e0 += E) {
-      T2 x;
-      x.t.blk = b;
-      x.t.e0 = e0;
-      x.t.ne = (int)std::min<long long>(E, B.d.n_elem - e0);
-      x.cost = w * x.t.ne;
-      tl.push_back(x);
-    }
+    const long long whole = B.d.n_elem / E;
+    const int rest = (int)(B.d.n_elem - whole * E);
+    if (whole > 0) runs.push_back(Run{b, E, 0, whole, w * E});
+    if (rest > 0) runs.push_back(Run{b, rest, whole * E, 1, w * rest});
+    ntiles += whole + (rest > 0);
   }
-  std::stable_sort(tl.begin(), tl.end(), [](const T2& a, const T2& b) { return a.cost > b.cost; });
-  if ((long long)tl.size() > p->max_tiles) return fail(SHP_ERR_WORKSPACE, "tile list overflow");
-  std::vector<Tile> host(tl.size());
-  for (size_t i = 0; i < tl.size(); ++i) host[i] = tl[i].t;
+  std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.cost > b.cost; });
+  if (ntiles > p->max_tiles) return fail(SHP_ERR_WORKSPACE, "tile list overflow");
+  std::vector<Tile> host(ntiles);
+  Tile* h = host.data();
+  for (const Run& r : runs)
+    for (long long i = 0; i < r.n; ++i, ++h) {
+      h->blk = r.blk;
+      h->ne = r.ne;
+      h->e0 = r.e0 + i * r.ne;
+    }
   Tile* dst = reinterpret_cast<Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
   hipError_t e = hipSuccess;
   if (!host.empty()) e = hipMemcpyAsync(dst, host.data(), sizeof(Tile) * host.size(), hipMemcpyHostToDevice, s);
@@ -928,6 +922,7 @@ static int build_tiles(shp_plan p, int opk, hipStream_t s) {
   p->mixed_ntiles[opk] = (int)host.size();
   p->mixed_now[opk] = mt;
   p->mixed_lds[opk] = lds;
+  p->mixed_lds32[opk] = lds32;
   p->mixed_dirty[opk] = false;
   return SHP_OK;
 }
@@ -1007,6 +1002,14 @@ static int resolve_auto(shp_plan p, int blk, int op, hipStream_t s, int* strateg
   return SHP_OK;
 }
 
+// whether work sent to s now is recorded into a graph (an upload cannot be)
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();  // the null stream, while another stream is captured
+  return true;
+}
+
 static bool unset_or(const Tiling& set, const Tiling& t) {
   return set.E <= 0 || set.NT <= 0 || (set.E == t.E && set.NT == t.NT && set.persist == t.persist);
 }
@@ -1017,14 +1020,14 @@ static bool unset_or(const Tiling& set, const Tiling& t) {
 // tuner runs as set.
 static bool mf_block_runs(const Block& B, int opk) {
   int E, NT;
-  if (!mf_action(opk) || is_2d(B.d.shape) || !mf_helm_shape(B.d.P, &E, &NT)) return false;
+  if (!helm_action(opk) || is_2d(B.d.shape) || !mf_helm_shape(B.d.P, &E, &NT)) return false;
   const Tiling& set = B.tiling[opk];
   return unset_or(set, Tiling{E, NT, 2}) || unset_or(set, default_tiling(B.d.shape, B.d.P, opk));
 }
 
 static bool mf_mesh_runs(shp_plan p, int opk) {
   int E, NT;
-  if (!mf_action(opk) || !mf_mesh(p) || !mf_helm_shape(p->blocks[0].d.P, &E, &NT)) return false;
+  if (!helm_action(opk) || !mf_mesh(p) || !mf_helm_shape(p->blocks[0].d.P, &E, &NT)) return false;
   const Tiling& set = p->mixed[opk];
   return unset_or(set, Tiling{E, NT, 2}) || unset_or(set, default_mixed(p, opk));
 }
@@ -1292,6 +1295,10 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
     return SHP_OK;
   }
   if (mf_mesh_runs(p, opk)) {
+    // this launch takes no tile list, but the FP32 action takes the same operator's:
+    // the first call of either builds it, so that the other can be captured
+    if (p->mixed_dirty[opk] && !capturing(s))
+      if (int r = build_tiles(p, opk, s)) return r;
     const hipError_t e = apply_mf(p, -1, opk, in, out, nullptr, lambda, s);
     if (e != hipSuccess) return dev_fail(e, "mixed launch");
     return SHP_OK;
@@ -1430,17 +1437,16 @@ int shp_apply_prec(shp_plan p, int blk, int op, int strategy, int prec, const vo
     if (is_2d(p->blocks[b].d.shape)) return fail(SHP_ERR_UNSUPPORTED, "FP32 contractions cover the 3D shapes");
   }
   const int opk = (op == SHP_OP_HELMHOLTZ) ? OPK_HELM : OPK_LAP;
-  const int tk = (op == SHP_OP_HELMHOLTZ) ? OPK_HELM_F32 : OPK_LAP_F32;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (p->mixed_dirty[tk])
-    if (int r = build_tiles(p, tk, s)) return r;
-  const Tiling mt = p->mixed_now[tk];
-  const size_t lds = p->mixed_lds[tk];
+  if (p->mixed_dirty[opk])
+    if (int r = build_tiles(p, opk, s)) return r;
+  const Tiling mt = p->mixed_now[opk];
+  const size_t lds = p->mixed_lds32[opk];
   if (points_per_thread((long long)mt.E * (p->blocks[0].d.Q) * p->blocks[0].d.Q * p->blocks[0].d.Q, mt.NT) == 0)
     return fail(SHP_ERR_UNSUPPORTED, "launch shape too large for the FP32 kernel's register slots");
-  const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)tk * p->max_tiles;
+  const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
   hipError_t e = launch_mixed_f32(p->blocks[0].d.P, opk, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat),
-                                  tiles, p->mixed_ntiles[tk], static_cast<const float*>(in), static_cast<float*>(out),
+                                  tiles, p->mixed_ntiles[opk], static_cast<const float*>(in), static_cast<float*>(out),
                                   lambda, mt.NT, lds, mt.E, p->fac32 != nullptr, s);
   if (e != hipSuccess) return dev_fail(e, "FP32 launch");
   return SHP_OK;
@@ -1949,7 +1955,7 @@ int shp_tune_cache_load(shp_plan p, const char* path, int* n_applied) {
       std::string sig;
       if (!json_str(l, "blocks", &sig) || sig != mixed_signature(p)) continue;
       p->mixed[opk] = Tiling{(int)E, (int)NT, (int)V};
-      drop_tiles(p, opk);
+      p->mixed_dirty[opk] = true;
       p->auto_mixed[op] = (int)st;
       p->auto_mixed_src[op] = 1;
       ++applied;

@@ -49,9 +49,7 @@ enum : int {
   OPK_IPR_LM = 16,    //   inner product
   OPK_DERIV_LM = 17,  //   physical derivative
   OPK_IPRD_LM = 18,   //   inner product with the derivatives
-  OPK_HELM_F32 = 19,  // tile lists of the FP32 actions (launch shapes of their own)
-  OPK_LAP_F32 = 20,
-  OPK_COUNT = 21
+  OPK_COUNT = 19
 };
 
 // Arguments of one block for one operator call.
