@@ -248,13 +248,6 @@ size_t iso_lds(int sh, int P) {
   return iso_shape(P).joint ? lds + sizeof(double) * 9 * (P + 2) * (P + 2) * qpad(P + 2) : lds;
 }
 
-void iso_add(IsoMesh& m, int blk, int P, long long n_elem) {
-  m.blk[m.nblk] = blk;
-  const long long end = m.wg0[m.nblk] + (n_elem + iso_shape(P).E - 1) / iso_shape(P).E;
-  ++m.nblk;
-  for (int i = m.nblk; i <= ISO_MAX_BLK; ++i) m.wg0[i] = end;  // no work-group is past the last block
-}
-
 // A launch of n_elem elements with fewer tiles than the chip has CUs takes smaller
 // ones (the transforms and the mass, whose tiles hold the most elements: 116
 // elements at P = 10, bwd + iprod + mass 34.8 us with 3 per work-group, 31 with 1), of
@@ -366,7 +359,7 @@ int shp_quadrature(int shape, int Q, int pts, double* xi, double* w) {
 
 int shp_plan_create(shp_plan* out, const shp_block_desc* blk, int nblk) {
   if (!out || !blk) return fail(SHP_ERR_INVALID_ARG, "null argument");
-  if (nblk < 1 || nblk > 64) return fail(SHP_ERR_INVALID_ARG, "nblk=%d outside [1,64]", nblk);
+  if (nblk < 1 || nblk > MAX_BLK) return fail(SHP_ERR_INVALID_ARG, "nblk=%d outside [1,%d]", nblk, MAX_BLK);
   for (int b = 0; b < nblk; ++b) {
     const shp_block_desc& d = blk[b];
     if (!valid_shape(d.shape)) return fail(SHP_ERR_INVALID_ARG, "block %d: bad shape %d", b, d.shape);
@@ -627,9 +620,10 @@ int shp_plan_set_geometry(shp_plan p, int blk, const double* jac, void* stream) 
                        hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return dev_fail(e, "coordinate copy");
     IsoMesh m{};
-    iso_add(m, blk, B.d.P, B.d.n_elem);
-    e = launch_iso_check(B.d.P, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), m,
-                         iso_lds(B.d.shape, B.d.P), status, s);
+    const long long ne = B.d.n_elem;
+    for (IsoCursor c; e == hipSuccess && iso_next(m, c, B.d.P, 1, &blk, &ne);)
+      e = launch_iso_check(B.d.P, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), m,
+                           iso_lds(B.d.shape, B.d.P), status, s);
     if (e != hipSuccess) return dev_fail(e, "iso-parametric geometry check launch");
   } else {
   GeomArgs g;
@@ -1179,20 +1173,21 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
         if (!p->blocks[b].geom_ok) return fail(SHP_ERR_STATE, "block %d: geometry not set", b);
       const int iopk = (opk == OPK_HELM) ? OPK_HELM_ISO : OPK_LAP_ISO;
       const BlockStatic* bst = reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat);
-      // the costlier shapes first, ISO_MAX_BLK blocks to a launch
+      // the costlier shapes first
       const std::vector<int> order = blk >= 0 ? std::vector<int>{blk} : cost_order(p);
-      hipError_t e = hipSuccess;
-      for (size_t i = 0; i < order.size() && e == hipSuccess;) {
-        IsoMesh m{};
-        m.whole = blk < 0;
-        size_t lds = 0;
-        for (; i < order.size() && m.nblk < ISO_MAX_BLK; ++i) {
-          const Block& B = p->blocks[order[i]];
-          lds = std::max(lds, iso_lds(B.d.shape, B.d.P));
-          iso_add(m, order[i], B.d.P, B.d.n_elem);
-        }
-        e = launch_iso(p->blocks[order[0]].d.P, iopk, bst, m, in, out, lambda, lds, s);
+      const int n = (int)order.size(), P = p->blocks[order[0]].d.P;
+      long long ne[MAX_BLK];
+      size_t lds = 0;
+      for (int i = 0; i < n; ++i) {
+        const Block& B = p->blocks[order[i]];
+        ne[i] = B.d.n_elem;
+        lds = std::max(lds, iso_lds(B.d.shape, P));
       }
+      IsoMesh m{};
+      m.whole = blk < 0;
+      hipError_t e = hipSuccess;
+      for (IsoCursor c; e == hipSuccess && iso_next(m, c, P, n, order.data(), ne);)
+        e = launch_iso(P, iopk, bst, m, in, out, lambda, lds, s);
       if (e != hipSuccess) return dev_fail(e, "iso-parametric launch");
       return SHP_OK;
     }

@@ -166,8 +166,39 @@ constexpr int ISO_MAX_BLK = 16;
 struct IsoMesh {
   int nblk, whole;  // whole: in/out are whole-mesh buffers, else block blk[0]'s
   int blk[ISO_MAX_BLK];
-  long long wg0[ISO_MAX_BLK + 1];
+  long long wg0[ISO_MAX_BLK + 1];  // wg0[0] = -w: blk[0] goes on after w work-groups of earlier launches
 };
+// The launches over n blocks (blk[i] of n_elem[i] elements, in this order): each call
+// fills m with the next one, from work-group wg of block i on, and moves (i, wg); false
+// when nothing is left.  A launch takes at most ISO_MAX_BLK blocks, and fewer than
+// 2^32 threads: an element per work-group exceeds that from 8 to 17 million elements,
+// which fit the memory as no factors are stored.
+struct IsoCursor {
+  int i = 0;
+  long long wg = 0;
+};
+inline bool iso_next(IsoMesh& m, IsoCursor& c, int P, int n, const int* blk, const long long* n_elem) {
+  const IsoShape sh = iso_shape(P);
+  const long long limit = 0xffffffffLL / sh.NT;
+  long long wgs = 0;
+  m.nblk = 0;
+  while (c.i < n && m.nblk < ISO_MAX_BLK && wgs < limit) {
+    const long long left = (n_elem[c.i] + sh.E - 1) / sh.E - c.wg;
+    const long long take = left < limit - wgs ? left : limit - wgs;
+    if (take > 0) {
+      m.blk[m.nblk] = blk[c.i];
+      m.wg0[m.nblk++] = wgs - c.wg;  // c.wg is zero but for the launch's first block
+    }
+    wgs += take;
+    c.wg += take;
+    if (take == left) {
+      ++c.i;
+      c.wg = 0;
+    }
+  }
+  for (int i = m.nblk; i <= ISO_MAX_BLK; ++i) m.wg0[i] = wgs;  // no work-group is past the last block
+  return wgs > 0;
+}
 hipError_t launch_iso(int P, int opk, const BlockStatic* blocks, const IsoMesh& m, const double* in, double* out,
                       double lambda, size_t lds, hipStream_t s);
 hipError_t launch_iso_check(int P, const BlockStatic* blocks, const IsoMesh& m, size_t lds, int* status,
@@ -202,6 +233,7 @@ int points_per_thread(long long points, int threads);
 hipError_t launch_maxdiff(const double* a, const double* b, long long n, unsigned long long* out, hipStream_t s);
 
 constexpr int MAX_P = 10;
+constexpr int MAX_BLK = 64;  // blocks of a plan
 constexpr size_t LDS_LIMIT = 160 * 1024;
 
 // Plan queries for the solver (shp_api.cpp): the mesh's coefficient count,

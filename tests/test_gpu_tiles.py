@@ -133,3 +133,38 @@ def test_streamed_launches(shp):
             y = y.reshape((3, ne, Q3) if op == "physderiv" else (ne, -1)).cpu().numpy()
             tail = y[:, -nb:] if op == "physderiv" else y[-nb:]
             assert np.array_equal(tail.reshape(yb.shape), yb), (op, blk)
+
+
+def test_iso_past_one_launch(shp):
+    """16.8 million tetrahedra of P = 4, one to a work-group of 256 threads, are more
+    than one launch takes (2^32 threads): the elements around the cut, and the block
+    after them, have the bits of a launch of their own and agree with the oracle."""
+    P, cut, half = 4, 2**24 - 1, 15
+    n, s = cut + 20, "tet"
+    say(f"[tiles] iso past one launch n_elem={n}")
+    X = {}
+    for b, (t, k) in enumerate((("hex", 5), ("tet", 64))):
+        idx, vxi = O.vertex_modes(t, P)
+        X[t] = torch.from_numpy(W.iso_coords(W.shape_batch(t, k), idx, vxi, O.num_modes(t, P), 980 + b, curved=True,
+                                             amp=0.02)).cuda()
+    big = shp.Plan([("hex", P, 5, "isoparam"), (s, P, n, "isoparam")])
+    big.set_geometry(0, X["hex"])
+    Xt = X[s].repeat(n // 64 + 1, 1, 1)[:n]
+    big.set_geometry(1, Xt)
+    x = torch.rand(big.totals()[0], dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(7))
+    y = big.apply(-1, "helmholtz", x, lam=1.1)
+    co, NP = big.offsets(1)[0], big.n_modes[1]
+    sel = slice(cut - half, cut + half)
+    small = shp.Plan([("hex", P, 5, "isoparam"), (s, P, 2 * half, "isoparam")])
+    small.set_geometry(0, X["hex"])
+    small.set_geometry(1, Xt[sel].contiguous())
+    xs = x[co:].reshape(n, NP)[sel].contiguous()
+    ys = small.apply(1, "helmholtz", xs, lam=1.1)
+    ref = O.apply_op("helmholtz", s, P, P + 2, O.isoparametric_jacobian(s, P, P + 2, Xt[sel].cpu().numpy()),
+                     xs.cpu().numpy(), lam=1.1, chunk=2)
+    assert rel(ys.cpu().numpy(), ref) <= TOL
+    assert torch.equal(y[co:].reshape(n, NP)[sel], ys)
+    assert torch.equal(y[:co], small.apply(0, "helmholtz", x[:co].reshape(5, -1), lam=1.1).reshape(-1))
+    assert torch.equal(big.apply(1, "helmholtz", x[co:].reshape(n, NP), lam=1.1).reshape(-1), y[co:])
+    del big, Xt, x, y
+    torch.cuda.empty_cache()
