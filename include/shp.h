@@ -379,13 +379,13 @@ typedef struct {
 
 /* Exhaustive tuning of operator op on block blk (-1: the whole-mesh launch):
  * "different implementation choices may be made per block" (Sec. 3.3).  Every
- * strategy and launch shape that fits (quick = 1: a reduced set) runs on the
- * caller's representative input in; its output must match the default
- * collocated launch's output (written to ref) to 1e-12 in the max norm
- * relative to max |ref| or it is rejected; accepted candidates are timed as the
- * median of reps launches (at most 64) with HIP events on stream, each launch
- * preceded, outside the events, by a write of a 1 GiB buffer that the call
- * allocates and frees, so that the 256 MiB Infinity Cache does not serve the
+ * strategy and launch shape that fits (quick = 1: a reduced set; the default
+ * shapes are in both) runs on the caller's representative input in; its output
+ * must match the default collocated launch's output (written to ref) to 1e-12
+ * in the max norm relative to max |ref| or it is rejected; accepted candidates
+ * are timed as the median of reps launches (at most 64) with HIP events on
+ * stream, each launch preceded, outside the events, by a write of a 1 GiB
+ * buffer that the call allocates and frees, so that the 256 MiB Infinity Cache does not serve the
  * inputs of small batches.  The fastest becomes the launch shape of its
  * strategy and the choice SHP_AUTO makes for (blk, op).  With blk = -1 on a
  * plan whose blocks differ in P the whole-mesh call runs one launch per block

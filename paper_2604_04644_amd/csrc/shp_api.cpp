@@ -1595,6 +1595,15 @@ int shp_tune(shp_plan p, int blk, int op, const double* in, double* out, double*
     std::vector<int> Vs = {0};
     if (helm && st == SHP_SUMFAC_COLL) Vs = quick ? std::vector<int>{0, 2, 3} : std::vector<int>{0, 1, 2, 3, 4};
     const bool lm = (st == SHP_LOCALMAT);  // one launch shape: 16 elements, 4 waves
+    // the launch of an untuned plan, whatever the lists hold (the quick ones lack the 512
+    // threads that it has at P = 9 and 10, where it is the matrix-core launch)
+    Tiling def;
+    if (!lm) {
+      def = blk >= 0 ? effective(Tiling{}, p->blocks[blk].d.shape, P, opk, p->blocks[blk].d.n_elem)
+                     : default_mixed(p, opk);
+      if (Vs.size() == 1) def.persist = 0;  // no variants
+      cands.push_back(Cand{si, def.E, def.NT, def.persist});
+    }
     for (int E : (lm ? std::vector<int>{16} : Es))
       for (int NT : (lm ? std::vector<int>{256} : NTs))
         for (int V : Vs) {
@@ -1607,6 +1616,7 @@ int shp_tune(shp_plan p, int blk, int op, const double* in, double* out, double*
           else
             for (const auto& B : p->blocks) fits = fits && op_lds_bytes(B.d.shape, B.d.P, opk, E, V) <= 64 * 1024 * 2;
           if (lm) fits = true;
+          if (E == def.E && NT == def.NT && V == def.persist) fits = false;  // in the list already
           if (fits) cands.push_back(Cand{si, E, NT, V});
         }
   }

@@ -72,3 +72,34 @@ def test_tune_whole_mesh_and_corrupt_cache(shp, tmp_path):
         f.write('{"kind":"mixed","device":"zz","prec":"fp64","op":6,"blocks":"bad","strategy":2,"E":999,"NT":7,"variant":9}\n')
     plan.save_tuning(path)
     assert plan.load_tuning(path) == 1       # only the valid mixed entry applies
+
+
+@pytest.mark.parametrize("P", [2, 7, 9, 10])
+def test_tune_tries_the_default(shp, P, tmp_path):
+    """Quick tuning times the launch of an untuned plan too (512 threads at P = 9 and 10,
+    where the Laplacian and Helmholtz actions run on the matrix cores), of a block and of
+    the whole mesh; as the choice, loaded into another plan, it gives the same bits."""
+    blocks = [("prism", 40), ("pyr", 60)]
+    plans = [shp.Plan([(s, P, n, "curved") for s, n in blocks]) for _ in range(2)]
+    for plan in plans:
+        for b, (s, n) in enumerate(blocks):
+            xi, _ = shp.quadrature(s, P + 2)
+            plan.set_geometry(b, torch.from_numpy(W.jacobian(W.shape_batch(s, n), xi, curved=True)).cuda())
+    plan, other = plans
+    for blk in (0, -1):
+        for op in ("helmholtz", "mass"):
+            print(f"[tune] default P={P} blk={blk} {op}", flush=True)
+            x = torch.from_numpy(W.coeffs(1, plan._in_numel(blk, op), 5)[0]).cuda()
+            y = plan.apply(blk, op, x, strategy="sumfac_coll")
+            shape = plan.get_tiling(blk, op)
+            res, recs = plan.tune(blk, op, x, reps=3, quick=True)
+            own = [r for r in recs if r["strategy"] == "sumfac_coll" and
+                   (r["elems_per_wg"], r["threads"], r["variant"]) == shape]
+            assert len(own) == 1 and own[0]["passed"], shape
+            assert res["ms"] <= own[0]["ms"]
+            path = str(tmp_path / f"{blk}{op}.jsonl")
+            plan.save_tuning(path)
+            assert other.load_tuning(path) >= 1
+            assert other.get_tiling(blk, op, res["strategy"]) == (res["elems_per_wg"], res["threads"], res["variant"])
+            plan.set_tiling(blk, op, *shape)
+            assert torch.equal(plan.apply(blk, op, x, strategy="sumfac_coll"), y)
