@@ -108,3 +108,25 @@ def test_helm_not_finite(shp, shape, P, n):
         assert np.isfinite(ok).all() and np.array_equal(y[rest], ok[rest])
         assert np.array_equal(y, line, equal_nan=True), lam
         assert not (lam < 1.0 or lam == 1e300) or not np.isfinite(y[k]).any()
+
+
+@pytest.mark.parametrize("P", [2, 6, 9, 10])
+def test_adr_mesh(shp, P):
+    """Advection-diffusion-reaction with a velocity that differs at every point, against
+    the oracle; blocks whose last tile is partial and clamps its velocity reads (P = 2,
+    8 elements a tile), and a block smaller than a tile."""
+    print(f"[mf] adr P={P}", flush=True)
+    blocks = [("tet", 11 if P == 2 else 3), ("hex", 5 if P == 2 else 2), ("pyr", 17 if P == 2 else 2),
+              ("prism", 9 if P == 2 else 3)]
+    plan, jo = plan_of(shp, blocks, P)
+    nc, npnt = plan.totals()
+    x = W.coeffs(1, nc, 61 + P)[0]
+    vel = W.point_values(1, npnt, 71 + P, ncomp=3).reshape(3, npnt)
+    adv = plan.advection_factors(torch.from_numpy(np.ascontiguousarray(vel)).cuda())
+    y = plan.apply_adr(torch.from_numpy(x).cuda(), adv, lam=1.3).cpu().numpy()
+    for b, (s, n) in enumerate(blocks):
+        co, po = plan.offsets(b)
+        NP, NQ = plan.n_modes[b], plan.n_points[b]
+        ref = O.apply_op("adr", s, P, P + 2, jo[b], x[co:co + n * NP].reshape(n, NP), lam=1.3,
+                         vel=vel[:, po:po + n * NQ].reshape(3, n, NQ))
+        assert rel(y[co:co + n * NP].reshape(n, NP), ref) <= TOL, s
