@@ -91,6 +91,8 @@ struct Block {
 
 }  // namespace
 
+constexpr int TILE_LISTS = 10;  // whole-mesh operators with a tile list (tile_list)
+
 struct shp_plan_s {
   std::vector<Block> blocks;
   size_t ws_bytes = 0;
@@ -98,7 +100,7 @@ struct shp_plan_s {
   float* fac32 = nullptr;  // caller's FP32 copy of the factors for the FP32 actions, or null
   size_t off_status = 0, off_bstat = 0, off_tiles = 0;
   long long total_elem = 0, total_coeff = 0, total_phys = 0;
-  long long max_tiles = 0;  // tile slots reserved per operator
+  long long max_tiles = 0;  // slots of a tile list
   Tiling mixed[OPK_COUNT];
   int mixed_ntiles[OPK_COUNT] = {};
   Tiling mixed_now[OPK_COUNT];        // launch shape and LDS that go with the tile list (build_tiles)
@@ -447,7 +449,7 @@ int shp_plan_create(shp_plan* out, const shp_block_desc* blk, int nblk) {
                                         3 * MODEL_MAX_MEMBERS));
   p->max_tiles = std::max<long long>(1, p->total_elem);
   p->off_tiles = off;
-  off = align_up(off + sizeof(Tile) * (size_t)p->max_tiles * OPK_COUNT);
+  off = align_up(off + sizeof(Tile) * (size_t)p->max_tiles * TILE_LISTS);
   for (auto& B : p->blocks) {
     B.off_tab = off;
     off = align_up(off + sizeof(double) * B.tab.size());
@@ -868,10 +870,19 @@ static std::vector<int> cost_order(shp_plan p) {
   return order;
 }
 
+// The tile list of whole-mesh operator opk: the sum-factorised operators, which come
+// first, and the advection-diffusion-reaction action have one (the local matrices and
+// the iso-parametric launches find their elements from the block sizes).
+static Tile* tile_list(shp_plan p, int opk) {
+  const int i = opk == OPK_ADR ? TILE_LISTS - 1 : opk;
+  return reinterpret_cast<Tile*>(p->ws + p->off_tiles) + (size_t)i * p->max_tiles;
+}
+
 // Build and upload the whole-mesh tile list of one operator: tiles of E
 // elements from every block, heaviest first (longest-processing-time order).
 // The FP32 actions run the list and the launch shape of the FP64 ones.
 static int build_tiles(shp_plan p, int opk, hipStream_t s) {
+  static_assert(TILE_LISTS == OPK_LAP_NC + 2, "a list for each sum-factorised operator, and the last one");
   const Tiling mt = mixed_tiling(p, opk);
   const int E = mt.E;
   size_t lds = 0, lds32 = 0;
@@ -908,7 +919,7 @@ static int build_tiles(shp_plan p, int opk, hipStream_t s) {
       h->ne = r.ne;
       h->e0 = r.e0 + i * r.ne;
     }
-  Tile* dst = reinterpret_cast<Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
+  Tile* dst = tile_list(p, opk);
   hipError_t e = hipSuccess;
   if (!host.empty()) e = hipMemcpyAsync(dst, host.data(), sizeof(Tile) * host.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1149,7 +1160,7 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
         if (int r = build_tiles(p, opk, s)) return r;
       const Tiling mt = p->mixed_now[opk];
       const size_t lds = p->mixed_lds[opk];
-      const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
+      const Tile* tiles = tile_list(p, opk);
       e = launch_mixed2d(p->blocks[0].d.P, opk, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), tiles,
                          p->mixed_ntiles[opk], in, out, p->total_phys, p->total_phys, lambda, mt.NT, lds, mt.E, s);
     }
@@ -1303,7 +1314,7 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
   const Tiling mt = p->mixed_now[opk];
   const int E = mt.E, NT = mt.NT;
   const size_t lds = p->mixed_lds[opk];
-  const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
+  const Tile* tiles = tile_list(p, opk);
   hipError_t e = launch_mixed(p->blocks[0].d.P, opk, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), tiles,
                               p->mixed_ntiles[opk], in, out, p->total_phys, p->total_phys, lambda, NT, lds, E, mt.persist,
                               streams_nt(opk, p->total_phys), s);
@@ -1439,7 +1450,7 @@ int shp_apply_prec(shp_plan p, int blk, int op, int strategy, int prec, const vo
   const size_t lds = p->mixed_lds32[opk];
   if (points_per_thread((long long)mt.E * (p->blocks[0].d.Q) * p->blocks[0].d.Q * p->blocks[0].d.Q, mt.NT) == 0)
     return fail(SHP_ERR_UNSUPPORTED, "launch shape too large for the FP32 kernel's register slots");
-  const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)opk * p->max_tiles;
+  const Tile* tiles = tile_list(p, opk);
   hipError_t e = launch_mixed_f32(p->blocks[0].d.P, opk, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat),
                                   tiles, p->mixed_ntiles[opk], static_cast<const float*>(in), static_cast<float*>(out),
                                   lambda, mt.NT, lds, mt.E, p->fac32 != nullptr, s);
@@ -1490,7 +1501,7 @@ int shp_apply_adr(shp_plan p, const double* adv, const double* in, double* out, 
   if (points_per_thread((long long)mt.E * Q * Q * Q, mt.NT) == 0)
     return fail(SHP_ERR_UNSUPPORTED, "launch shape too large for the advection-diffusion-reaction kernel");
   const size_t lds = p->mixed_lds[OPK_ADR];
-  const Tile* tiles = reinterpret_cast<const Tile*>(p->ws + p->off_tiles) + (size_t)OPK_ADR * p->max_tiles;
+  const Tile* tiles = tile_list(p, OPK_ADR);
   const hipError_t e = launch_adr(p->blocks[0].d.P, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), tiles,
                                   p->mixed_ntiles[OPK_ADR], in, out, adv, lambda, mt.NT, lds, mt.E, s);
   if (e != hipSuccess) return dev_fail(e, "advection-diffusion-reaction launch");

@@ -290,3 +290,25 @@ def test_2d_plan_rules_without_device(L):
     assert L.shp_get_tiling(h, 0, 6, 2, ctypes.byref(E), ctypes.byref(NT), ctypes.byref(pe)) == 0
     assert (E.value, NT.value) == (8, 256)
     L.shp_plan_destroy(h)
+
+
+def test_workspace_per_element(L):
+    """An element's share of the workspace: its coordinates or factors, and 16 bytes in
+    each of the ten tile lists (nine sum-factorised operators and
+    advection-diffusion-reaction; local matrices and iso-parametric launches have none)."""
+    from paper_2604_04644_amd import shp
+
+    def nbytes(shape, P, n, geom):
+        arr = (shp._BlockDesc * 1)(shp._BlockDesc(shp.SHAPES[shape], P, P + 2, n, shp.GEOM[geom], 0))
+        h, nb = ctypes.c_void_p(), ctypes.c_size_t()
+        assert L.shp_plan_create(ctypes.byref(h), ctypes.cast(arr, ctypes.c_void_p), 1) == 0
+        assert L.shp_plan_workspace_bytes(h, ctypes.byref(nb)) == 0
+        L.shp_plan_destroy(h)
+        return nb.value
+
+    n = 1 << 16
+    for shape in O.SHAPES:
+        for P in (1, 4, 10):
+            held = {"isoparam": 8 * 3 * shp.num_modes(shape, P), "curved": 8 * 16 * (P + 2) ** 3}
+            for geom, b in held.items():
+                assert nbytes(shape, P, 2 * n, geom) - nbytes(shape, P, n, geom) == n * (b + 16 * 10), (shape, P, geom)
