@@ -72,7 +72,7 @@ struct Block {
   std::vector<int> ditab;   //   and their pair and mode indices
   DiagDims dn;
   size_t off_dtab = 0, off_ditab = 0;
-  std::vector<double> mf;   // table image of the matrix-core stages
+  std::vector<double> mf;   // table image of the matrix-core launch, where the order has one
   size_t off_mf = 0;
   std::vector<double> wref; // iso-parametric blocks: reference weights [Q^3]
   size_t off_xco = 0, off_wref = 0;
@@ -406,7 +406,8 @@ int shp_plan_create(shp_plan* out, const shp_block_desc* blk, int nblk) {
     B.NP = num_modes(B.d.shape, B.d.P);
     B.NQ = B.d.Q * B.d.Q * B.d.Q;
     build_tables(B.d.shape, B.d.P, B.d.pts, B.tab, B.itab);
-    build_mf_image(B.d.shape, B.d.P, B.tab, B.itab, B.mf);
+    int mfE, mfNT;
+    if (!B.iso() && mf_helm_shape(B.d.P, &mfE, &mfNT)) build_mf_image(B.d.shape, B.d.P, B.tab, B.itab, B.mf);
     build_diag_tables(B.d.shape, B.d.P, B.d.pts, B.dtab, B.ditab, B.dn.n1, B.dn.n12);
     for (int i = 0; i < B.dn.n12; ++i) B.dn.n2 = std::max(B.dn.n2, (B.ditab[i] >> 16) + 1);
     B.dn.n3 = (int)B.dtab.size() / (3 * B.d.Q) - B.dn.n1 - B.dn.n2;
