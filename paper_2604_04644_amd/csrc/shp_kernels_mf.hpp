@@ -456,8 +456,12 @@ __device__ void helm_tile(const double* __restrict__ img, const double* __restri
         const int i = 4 * b + w.lr;
         const int off = (e < ne && i < Q) ? (e * (NFAC * Q3) + i * Q2 + jk) * 8 : E * (NFAC * Q3 * 8);
 #pragma unroll
-        for (int c = 0; c < NFAC; ++c)
-          g[s][b][c] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, off + c * Q3 * 8, 0, AUX));
+        for (int c = 0; c < NFAC; ++c) {
+          // the Laplacian does without jw: a seventh of the factors, not read (with it,
+          // 93750 hexahedra at P = 2 took as long as the Helmholtz action, 60 us)
+          const int o = c == 0 && !react ? E * (NFAC * Q3 * 8) : off + c * Q3 * 8;
+          g[s][b][c] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, o, 0, AUX));
+        }
       }
     }
   });
