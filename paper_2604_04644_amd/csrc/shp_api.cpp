@@ -268,14 +268,19 @@ Tiling spread(Tiling t, long long n_elem, int opk) {
 // weights: 24 bytes a point) exceeds it, 11.2M points.  P = 4 mesh, ordinary /
 // non-temporal, us: bwd + iprod + mass on their own fields 6.5M points 81 / 76, 11.2M
 // 138 / 116, 26.5M 299 / 247; bwd, a pass over its result and iprod 68 / 75, 111 / 109,
-// 270 / 255 (iprod repeated on one field alone: 36 / 41 at 11.2M, 98 / 91 at 26.5M).
+// 270 / 255.  The inner product repeated alone on one field still finds it in the cache
+// there and loses (36 / 41 at 11.2M; 98 / 91 at 26.5M): the line is drawn for fields
+// that are new.
 // Derivatives (104 bytes a point) from 4M points: both on their own fields, P = 5,
 // 2.1M 88 / 90, 3.1M 139 / 129, 5.2M 227 / 205, 10.3M 420 / 391; one after the other
-// with a pass between 93 / 115, 147 / 161, 261 / 251, 512 / 477.
-bool streams_nt(int opk, long long n_points) {
+// with a pass between 93 / 115, 147 / 161, 261 / 251, 512 / 477.  Not at P = 1: an
+// element's 27 points of a component are 216 bytes, so most cache lines are shared by
+// two components, whose loads then fetch them twice (12M points, derivatives 236 / 278,
+// inner product with derivatives 239 / 254; P = 2, 64 points, 122 / 111 at 6M).
+bool streams_nt(int opk, int P, long long n_points) {
   constexpr long long MIB = 1LL << 20;
   if (values_op(opk)) return 24 * n_points > 256 * MIB;
-  return (opk == OPK_DERIV || opk == OPK_IPRD) && 104 * n_points > 400 * MIB;
+  return (opk == OPK_DERIV || opk == OPK_IPRD) && P > 1 && 104 * n_points > 400 * MIB;
 }
 
 Tiling effective(const Tiling& set, int sh, int P, int opk, long long n_elem) {
@@ -1088,7 +1093,7 @@ static hipError_t apply_block(shp_plan p, int blk, int opk, const double* in, do
   a.out_cs = cs;
   a.lambda = lambda;
   a.E = t.E;
-  a.nt = streams_nt(opk, B.d.n_elem * (long long)B.NQ);
+  a.nt = streams_nt(opk, B.d.P, B.d.n_elem * (long long)B.NQ);
   return launch_block(B.d.shape, B.d.P, opk, a, t.NT, t.persist, s);
 }
 
@@ -1318,7 +1323,7 @@ int shp_apply(shp_plan p, int blk, int op, int strategy, const double* in, doubl
   const Tile* tiles = tile_list(p, opk);
   hipError_t e = launch_mixed(p->blocks[0].d.P, opk, reinterpret_cast<const BlockStatic*>(p->ws + p->off_bstat), tiles,
                               p->mixed_ntiles[opk], in, out, p->total_phys, p->total_phys, lambda, NT, lds, E, mt.persist,
-                              streams_nt(opk, p->total_phys), s);
+                              streams_nt(opk, p->blocks[0].d.P, p->total_phys), s);
   if (e != hipSuccess) return dev_fail(e, "mixed launch");
   return SHP_OK;
 }
