@@ -1021,9 +1021,8 @@ static bool capturing(hipStream_t s) {
   return true;
 }
 
-static bool unset_or(const Tiling& set, const Tiling& t) {
-  return set.E <= 0 || set.NT <= 0 || (set.E == t.E && set.NT == t.NT && set.persist == t.persist);
-}
+static bool same(const Tiling& a, const Tiling& b) { return a.E == b.E && a.NT == b.NT && a.persist == b.persist; }
+static bool unset(const Tiling& t) { return t.E <= 0 || t.NT <= 0; }
 
 // Whether the matrix-core launch takes operator opk: at the orders that have one it
 // stands in for the thread-per-line tile of the default launch shape (same bits, see
@@ -1033,14 +1032,20 @@ static bool mf_block_runs(const Block& B, int opk) {
   int E, NT;
   if (!helm_action(opk) || is_2d(B.d.shape) || !mf_helm_shape(B.d.P, &E, &NT)) return false;
   const Tiling& set = B.tiling[opk];
-  return unset_or(set, Tiling{E, NT, 2}) || unset_or(set, default_tiling(B.d.shape, B.d.P, opk));
+  if (same(set, Tiling{E, NT, 2})) return true;
+  // the Laplacian of hexahedra at P = 2: one eta3 family, so that the thread-per-line tile
+  // leaves no lanes idle.  Thread per line / here, us: 4687 elements 7.0 / 6.9, 6250 7.3 /
+  // 7.9, 20312 13.2 / 15.2, 46875 27.7 / 29.5, 203125 111 / 118 (the Helmholtz action at
+  // 9375 9.8 / 9.4, 15625 12.0 / 12.6, 46875 30.7 / 30.7, 203125 128 / 129: it stays)
+  if (opk == OPK_LAP && B.d.P == 2 && B.d.shape == SHP_HEX && B.d.n_elem > 5000) return false;
+  return unset(set) || same(set, default_tiling(B.d.shape, B.d.P, opk));
 }
 
 static bool mf_mesh_runs(shp_plan p, int opk) {
   int E, NT;
   if (!helm_action(opk) || !mf_mesh(p) || !mf_helm_shape(p->blocks[0].d.P, &E, &NT)) return false;
   const Tiling& set = p->mixed[opk];
-  return unset_or(set, Tiling{E, NT, 2}) || unset_or(set, default_mixed(p, opk));
+  return unset(set) || same(set, Tiling{E, NT, 2}) || same(set, default_mixed(p, opk));
 }
 
 static MfBlock mf_block(shp_plan p, int blk, const double* in, double* out) {

@@ -130,3 +130,21 @@ def test_adr_mesh(shp, P):
         ref = O.apply_op("adr", s, P, P + 2, jo[b], x[co:co + n * NP].reshape(n, NP), lam=1.3,
                          vel=vel[:, po:po + n * NQ].reshape(3, n, NQ))
         assert rel(y[co:co + n * NP].reshape(n, NP), ref) <= TOL, s
+
+
+@pytest.mark.parametrize("n", [5000, 5001])
+def test_hex_laplacian_rule(shp, n):
+    """Hexahedra at P = 2 on both sides of the size from which their Laplacian runs a thread
+    per line: the default launch, the matrix-core shape and a thread-per-line shape have
+    the same bits, and the last elements agree with the oracle."""
+    print(f"[mf] hex laplacian n={n}", flush=True)
+    P = 2
+    plan, jo = plan_of(shp, [("hex", n)], P)
+    x = W.coeffs(n, plan.n_modes[0], 23)
+    xt = torch.from_numpy(x).cuda()
+    y = plan.apply(0, "laplacian", xt)
+    for shape in ((8, 256, 2), (16, 256, 2), (1, 64, 0)):
+        plan.set_tiling(0, "laplacian", *shape)
+        assert torch.equal(plan.apply(0, "laplacian", xt), y), shape
+    ref = O.apply_op("laplacian", "hex", P, P + 2, jo[0][-9:], x[-9:])
+    assert rel(y[-9:].cpu().numpy(), ref) <= TOL
