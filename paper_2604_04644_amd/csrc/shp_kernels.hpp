@@ -973,25 +973,17 @@ __device__ void deriv_tile(const OpArgs& a, long long e0, int ne, const Tile_<SH
 
 // The tile of the other collocated operators: the stages read their tables through
 // the constant path except the tet's eta2 table and the column table, which
-// are all the (compact) LDS head holds.
-template <int SH, int P, int OP, typename R>
+// are all the (compact) LDS head holds.  NT: non-temporal streams, a kernel of its own.
+template <int SH, int P, int OP, bool NT, typename R>
 __device__ void tile_body(const OpArgs& a, long long e0, int ne, const Tile_<SH, P, R>& T) {
   using D = Dims<SH, P>;
   constexpr int Q3 = D::Q3;
-  // (hipcc 7.2 cannot compile the whole-mesh kernel of P = 10 with both forms in it:
-  // that order keeps ordinary accesses)
   if constexpr (values_op(OP)) {
-    if (P < 10 && a.nt)
-      values_tile<true, OP>(a, e0, ne, T);
-    else
-      values_tile<false, OP>(a, e0, ne, T);
+    values_tile<NT, OP>(a, e0, ne, T);
     return;
   }
   if constexpr (OP == OPK_DERIV || OP == OPK_IPRD) {
-    if (P < 10 && a.nt)
-      deriv_tile<true, OP>(a, e0, ne, T);
-    else
-      deriv_tile<false, OP>(a, e0, ne, T);
+    deriv_tile<NT, OP>(a, e0, ne, T);
     return;
   }
   load_tables_helm<SH, P>(a, T);
@@ -1124,7 +1116,7 @@ __device__ Tile_<SH, P> make_tile3(double* smem, const double* gtab) {
 }
 
 // one tile per work-group, tiles of one block
-template <int SH, int P, int OP>
+template <int SH, int P, int OP, bool NT = false>
 __global__ void __launch_bounds__(512) k_block(OpArgs a) {
   extern __shared__ double smem[];
   const long long e0 = (long long)blockIdx.x * a.E;
@@ -1132,16 +1124,16 @@ __global__ void __launch_bounds__(512) k_block(OpArgs a) {
   const int ne = rem < a.E ? (int)rem : a.E;
   if (ne <= 0) return;
   const Tile_<SH, P> T = make_tile_op<SH, P, OP, double>(smem, a.tab);
-  tile_body<SH, P, OP>(a, e0, ne, T);
+  tile_body<SH, P, OP, NT>(a, e0, ne, T);
 }
 
 // Mixed-shape launch: one tile per work-group from a tile list that spans every
 // block (all blocks share P).  Block b's part of the whole-mesh buffers starts
 // at its coefficient or point offset.
-template <int P, int OP>
+template <int P, int OP, bool NT = false>
 __global__ void __launch_bounds__(512) k_mixed(const BlockStatic* __restrict__ blocks, const Tile* __restrict__ tiles,
                                                int ntiles, const double* in, double* out, long long in_cs,
-                                               long long out_cs, double lambda, int nt) {
+                                               long long out_cs, double lambda) {
   extern __shared__ double smem[];
   const int ti = blockIdx.x;
   if (ti >= ntiles) return;
@@ -1162,12 +1154,12 @@ __global__ void __launch_bounds__(512) k_mixed(const BlockStatic* __restrict__ b
   a.out_cs = out_cs;
   a.lambda = lambda;
   a.E = b.E;
-  a.nt = nt;
+  a.nt = NT;
   switch (b.shape) {
-    case HEX: tile_body<HEX, P, OP>(a, tl.e0, tl.ne, make_tile_op<HEX, P, OP, double>(smem, a.tab)); break;
-    case PRISM: tile_body<PRISM, P, OP>(a, tl.e0, tl.ne, make_tile_op<PRISM, P, OP, double>(smem, a.tab)); break;
-    case PYR: tile_body<PYR, P, OP>(a, tl.e0, tl.ne, make_tile_op<PYR, P, OP, double>(smem, a.tab)); break;
-    default: tile_body<TET, P, OP>(a, tl.e0, tl.ne, make_tile_op<TET, P, OP, double>(smem, a.tab)); break;
+    case HEX: tile_body<HEX, P, OP, NT>(a, tl.e0, tl.ne, make_tile_op<HEX, P, OP, double>(smem, a.tab)); break;
+    case PRISM: tile_body<PRISM, P, OP, NT>(a, tl.e0, tl.ne, make_tile_op<PRISM, P, OP, double>(smem, a.tab)); break;
+    case PYR: tile_body<PYR, P, OP, NT>(a, tl.e0, tl.ne, make_tile_op<PYR, P, OP, double>(smem, a.tab)); break;
+    default: tile_body<TET, P, OP, NT>(a, tl.e0, tl.ne, make_tile_op<TET, P, OP, double>(smem, a.tab)); break;
   }
 }
 

@@ -168,3 +168,28 @@ def test_iso_past_one_launch(shp):
     assert torch.equal(big.apply(1, "helmholtz", x[co:].reshape(n, NP), lam=1.1).reshape(-1), y[co:])
     del big, Xt, x, y
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("s,P,ne", [("hex", 2, 175_003), ("prism", 10, 6_501)])
+def test_streamed_launches_orders(shp, s, P, ne):
+    """As above where the derivatives are streamed as well (from P = 2), and at the last
+    order: the last 5 elements of a block and of a whole-mesh launch."""
+    nb, Q3, NP = 5, (P + 2) ** 3, O.num_modes(s, P)
+    say(f"[tiles] streamed launches {s} P={P} n_elem={ne}")
+    maps = W.shape_batch(s, ne)
+    last = maps.take(np.arange(ne - nb, ne))
+    big, small = shp.Plan([(s, P, ne, "affine")]), shp.Plan([(s, P, nb, "affine")])
+    big.set_geometry(0, torch.from_numpy(W.affine_jacobian(maps)).cuda())
+    small.set_geometry(0, torch.from_numpy(W.affine_jacobian(last)).cuda())
+    g = torch.Generator("cuda").manual_seed(11)
+    for op in ("bwd", "iprod", "mass", "physderiv", "iprod_deriv"):
+        shape = {"iprod": (ne, Q3), "physderiv": (ne, Q3), "iprod_deriv": (3, ne, Q3)}.get(op, (ne, NP))
+        x = 2.0 * torch.rand(*shape, generator=g, device="cuda", dtype=torch.float64) - 1.0
+        xb = x[..., -nb:, :].contiguous()
+        yb = small.apply(0, op, xb).cpu().numpy()
+        ref = O.apply_op(op, s, P, P + 2, W.affine_jacobian(last), xb.cpu().numpy())
+        assert rel(yb.reshape(ref.shape), ref) <= TOL, op
+        for blk in (0, -1):
+            y = big.apply(blk, op, x.reshape(-1) if blk < 0 else x).reshape(
+                (3, ne, Q3) if op == "physderiv" else (ne, -1))[..., -nb:, :].cpu().numpy()
+            assert np.array_equal(y.reshape(yb.shape), yb), (op, blk)
