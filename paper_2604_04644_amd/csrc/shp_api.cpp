@@ -254,10 +254,16 @@ size_t iso_lds(int sh, int P) {
 // ones (the transforms and the mass, whose tiles hold the most elements: 116
 // elements at P = 10, bwd + iprod + mass 34.8 us with 3 per work-group, 31 with 1), of
 // 512 threads: the eta3 families of stage r are dealt to more waves (60 elements,
-// 256 / 512 threads, mass at P = 4 6.0 / 5.7 us, 6 8.1 / 7.4, 8 10.9 / 9.7).
-Tiling spread(Tiling t, long long n_elem, int opk) {
+// 256 / 512 threads, mass at P = 4 6.0 / 5.7 us, 6 8.1 / 7.4, 8 10.9 / 9.7).  Up to two
+// tiles a CU the threads alone are doubled, from P = 4 on (mesh, bwd / iprod / mass, us:
+// P = 5 1740 elements 5.6 / 5.5 / 7.9 and 5.3 / 5.2 / 7.6 with 512, P = 6 1950 6.9 / 6.2 / 9.3
+// and 6.5 / 5.9 / 8.6, P = 8 600 7.8 / 7.8 / 11.4 and 6.9 / 7.3 / 10.7; four tiles a CU, P = 6
+// 3900, 8.8 / 9.2 / 12.2 and 10.5 / 12.0 / 15.8; P = 2 6240 elements 4.0 / 3.9 / 4.9 and 4.0 /
+// 3.9 / 5.0).
+Tiling spread(Tiling t, int P, long long n_elem, int opk) {
   constexpr int CUS = 256;
-  if (!values_op(opk) || n_elem >= (long long)CUS * t.E) return t;
+  if (!values_op(opk) || n_elem > 2LL * CUS * t.E) return t;
+  if (n_elem >= (long long)CUS * t.E) return P >= 4 ? Tiling{t.E, 512, t.persist} : t;
   return Tiling{(int)std::max<long long>(1, (n_elem + CUS - 1) / CUS), 512, t.persist};
 }
 
@@ -286,7 +292,7 @@ bool streams_nt(int opk, int P, long long n_points) {
 Tiling effective(const Tiling& set, int sh, int P, int opk, long long n_elem) {
   if (set.E > 0 && set.NT > 0) return set;
   const Tiling t = default_tiling(sh, P, opk);
-  return is_2d(sh) ? t : spread(t, n_elem, opk);
+  return is_2d(sh) ? t : spread(t, P, n_elem, opk);
 }
 
 int check_plan(shp_plan p) {
@@ -849,7 +855,7 @@ static Tiling default_mixed(shp_plan p, int opk) {
     t.NT = std::min(t.NT, d.NT);
     t.persist = std::min(t.persist, d.persist);
   }
-  return dim2 ? t : spread(t, p->total_elem, opk);
+  return dim2 ? t : spread(t, P0, p->total_elem, opk);
 }
 
 static Tiling mixed_tiling(shp_plan p, int opk) {
