@@ -1039,11 +1039,12 @@ static bool mf_block_runs(const Block& B, int opk) {
   if (!helm_action(opk) || is_2d(B.d.shape) || !mf_helm_shape(B.d.P, &E, &NT)) return false;
   const Tiling& set = B.tiling[opk];
   if (same(set, Tiling{E, NT, 2})) return true;
-  // the Laplacian of hexahedra at P = 2: one eta3 family, so that the thread-per-line tile
-  // leaves no lanes idle.  Thread per line / here, us: 4687 elements 7.0 / 6.9, 6250 7.3 /
-  // 7.9, 20312 13.2 / 15.2, 46875 27.7 / 29.5, 203125 111 / 118 (the Helmholtz action at
-  // 9375 9.8 / 9.4, 15625 12.0 / 12.6, 46875 30.7 / 30.7, 203125 128 / 129: it stays)
-  if (opk == OPK_LAP && B.d.P == 2 && B.d.shape == SHP_HEX && B.d.n_elem > 5000) return false;
+  // the Laplacian of hexahedra at P = 2, which have one eta3 family, so that the
+  // thread-per-line tile leaves no lanes idle; a second round of tiles here (8 elements, 256
+  // CUs) costs what the first one does.  Thread per line / here, us: 1562 elements 5.4 / 4.9,
+  // 2343 5.7 / 6.2, 4687 7.0 / 6.9, 20312 13.2 / 15.2, 46875 27.7 / 29.5, 203125 111 / 118 (the
+  // Helmholtz action at 9375 9.8 / 9.4, 15625 12.0 / 12.6, 203125 128 / 129: it stays)
+  if (opk == OPK_LAP && B.d.P == 2 && B.d.shape == SHP_HEX && B.d.n_elem > 2048) return false;
   return unset(set) || same(set, default_tiling(B.d.shape, B.d.P, opk));
 }
 

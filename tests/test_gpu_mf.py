@@ -132,7 +132,7 @@ def test_adr_mesh(shp, P):
         assert rel(y[co:co + n * NP].reshape(n, NP), ref) <= TOL, s
 
 
-@pytest.mark.parametrize("n", [5000, 5001])
+@pytest.mark.parametrize("n", [2048, 2049])
 def test_hex_laplacian_rule(shp, n):
     """Hexahedra at P = 2 on both sides of the size from which their Laplacian runs a thread
     per line: the default launch, the matrix-core shape and a thread-per-line shape have
