@@ -16,14 +16,15 @@
 //     s0 = uu c0 + uw c1, s1 = uu c2                           (phase 1)
 //   eta3, per mode: uu s0 (phase 0) + uw s0 + ww s1 (phase 1).
 //
-// The launch reads each factor from HBM once and should run at the copy rate.  The
-// eta1 stage gives a lane one line (j, k), its fields' Q values in registers and
-// the products as scalar operands; two waves share a line's factors a, so that
-// an element has six tasks for the wave's 64 lines.  Products are tabulated per
-// distinct factor and kept in LDS for eta2 and eta3 over the elements of a
-// work-group (formed from global tables at every use, with Q a run-time value,
-// the launch took 800 us for 15360 elements at P = 6 where the factors' bytes
-// need 95).
+// The launch reads each factor from HBM once.  15360 elements at P = 6 take 214 us where
+// the factors' bytes need 95: eta2 reads 3 Q sums and 3 Q products from LDS for one or
+// two results, and three waves a SIMD do not cover it (LDS busy 51 % of the time, 18 in
+// bank conflicts, VALU 18 %).  The eta1 stage gives a lane one line (j, k), its fields'
+// Q values in registers and the products as scalar operands; two waves share a line's
+// factors a, so that an element has six tasks for the wave's 64 lines.  Products are
+// tabulated per distinct factor and kept in LDS for eta2 and eta3 over the elements of a
+// work-group (formed from global tables at every use, with Q a run-time value, the
+// launch took 800 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -815,7 +815,7 @@ __device__ void ipr_chain(const Tile_<SH, P, R>& T, int ne, int mask) {
 // (P = 4: 2.6 KB per element in place of the 6.9 KB of four point buffers), and
 // points are read and written straight from global memory, consecutive lanes on
 // consecutive points (j, k).  With the points staged through LDS the launches
-// waited on 5, 6 and 9 barriers instead of 3, 4 and 6 and reached a third of the
+// waited on 4, 5 and 8 barriers instead of 3, 3 and 6 and reached a third of the
 // copy rate.  U holds the modes, the rows G and the result's modes, G(e, 0) the columns.
 template <int SH, int P>
 constexpr int values_bs() {

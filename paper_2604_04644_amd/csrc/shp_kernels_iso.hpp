@@ -160,8 +160,8 @@ __device__ __forceinline__ void iso_helm(const BlockStatic& b, const Tile& tl, c
 // tile: a stage has 4 Q^2 line tasks, one per thread, and the work-group waits on 11
 // barriers instead of 28.  A coordinate takes three point buffers, G2 in place of U:
 // 13 buffers an element against 16 (P = 4, 13.9k elements of mixed shapes: 103.7 us one
-// field after the other, 91 with 16 buffers, 87 with 13).  At P = 4 the LDS is busy 60 %
-// and the FP64 pipes 45 % of the time, 20-28 waves to a CU; padding the fields against
+// field after the other, 91 with 16 buffers, 87 with 13).  At P = 4 the LDS is busy 61 %
+// and the VALU 51 % of the time, 20 waves to a CU; padding the fields against
 // bank conflicts changed nothing, 16-byte line accesses cost 4 us.
 
 // the tile of the fields: field c at c * per

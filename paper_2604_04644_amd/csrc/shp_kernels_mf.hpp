@@ -28,9 +28,9 @@
 // element instead of four).
 //
 // What bounds the tile: LDS and the matrix cores take turns rather than overlap,
-// since all waves of a work-group are in the same stage (P = 8, counters: LDS
-// active 54 % of the time, matrix cores 28 %, VALU 26 %), so what matters is the
-// padding.  Helmholtz on the mixed mesh (1 hex : 2 prisms : 6 pyramids : 6 tets,
+// since all waves of a work-group are in the same stage (counters, P = 6 mesh: LDS
+// busy 70 % of the time, matrix cores 24 %, VALU 32 %; P = 10 prisms 47, 20 and 17),
+// so what matters is the padding.  Helmholtz on the mixed mesh (1 hex : 2 prisms : 6 pyramids : 6 tets,
 // 8M points), thread-per-line / here, us:
 //   P = 2 93 / 79, 6 119 / 95, 9 214 / 131, 10 220 / 141;
 //   P = 1 101 / 104, 3 100 / 129, 4 114 / 125, 5 130 / 136, 7 150 / 156, 8 153 / 154.
